@@ -116,6 +116,7 @@ int build_views(const tsr_scene* sc, const tsr_intrinsics* intr, int n_views, Vi
     pix += (int64_t)c.width * c.height;
   }
   if (tiles >= (1ll << 31)) return fail(TSR_EINVAL, "too many tiles");
+  for (int v = n_views; v < TSR_MAX_VIEWS; ++v) vt->v[v].tile_off = 0x7fffffff;     // see view_of_tile
   vt->n_views = n_views;
   vt->n_tiles = (int32_t)tiles;
   vt->n_faces = sc->n_faces;

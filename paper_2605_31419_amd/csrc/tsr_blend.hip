@@ -4,13 +4,23 @@
 //
 // Work mapping: one 256-lane workgroup per 16x16 tile, one pixel per lane; wave w owns the
 // 8x8 quadrant (w & 1, w >> 1), so a face whose pixel rectangle misses a quadrant is skipped
-// by that wave with one scalar test.  Face records are staged in LDS in batches of kBatch,
-// loaded once per workgroup with coalesced 16-byte loads and read by all lanes as broadcasts.
+// by that wave with one scalar test.  Face records are staged in LDS in batches of kBatch by
+// loads that go straight to LDS, and read by all lanes as broadcasts.
+//
+// What bounds the walks (1200x680 view of 1M faces, fused kernel): a wave alone on its SIMD issues
+// one instruction in about five cycles, so the longest tile's four waves take about 0.37 us per
+// listed face whatever else runs (514 faces: 211 us of a 212 us launch before the walks took two
+// faces per round, 160 of 171 now), and below that the number of VALU instructions per visit.
+// Two faces per round, records loaded a face ahead, the paired gradient sums of tsr_device.h
+// and the staging without registers (72 -> 84 VGPRs instead of 120) took the step from 278 to
+// 244 us, the 8-view window of 500k faces from 700 to 641 us, the photometric step from 368 to
+// 335 us and the face statistics from 139 to 125 us.
 #include "tsr_internal.h"
 
 namespace tsr {
 
 constexpr int kBatch = 64;                 // faces per hit mask (one lane each)
+constexpr int kSlots = kBatch + 1;         // staged slots per batch: its faces and one empty record
 constexpr int kSpan = 256;                 // faces staged at once by a cooperative workgroup
 constexpr int kSepSpan = 128;              // ... in the separate forward and backward kernels
 constexpr int kWaves = kBlock / kWave;     // waves per workgroup: one per 8x8 quadrant
@@ -69,13 +79,13 @@ struct NormalIn {
   int64_t M;
 };
 
-// Window value for rho in (0, 1): I = rho^sigma (eq. 3).
+// Window value for rho clamped to [0, 1]: I = rho^sigma (eq. 3).
 template <int SM>
 __device__ __forceinline__ float window_pow(float rho, float sigma) {
   if constexpr (exp_mode<SM>() == 1) return rho;
   else if constexpr (exp_mode<SM>() == 2) return __builtin_sqrtf(rho);
   else if constexpr (exp_mode<SM>() == 3) return rho * rho;
-  else return exp2f(sigma * log2f(rho));
+  else return rho > 0.f ? exp2f(sigma * log2f(rho)) : 0.f;       // (an empty record's sigma is 0)
 }
 
 // The exponent a face is evaluated with: its record's in mode 4, else the launch's.
@@ -86,22 +96,30 @@ __device__ __forceinline__ float face_sigma(const float* r, float sigma) {
 }
 
 struct PixelEval {
-  float rho, I, alpha, c0, c1, c2;
+  float rho, I, alpha, c0, c1, c2;   // I and alpha: 0 (alpha: or not above 0) where the pixel is not covered
   float zp;        // depth blended into D: z_F, or 1 / W (perspective-correct; then also 1 / W
                    // of the colour's numerators), 0 where the face does not cover the pixel
-  bool k0, k1;     // the edge attaining the minimum of E_k is edge 0 / edge 1 (lowest index on
-                   // ties; edge 2 when neither)
+  bool k0, k1;     // E_0, E_1 attain the minimum of E_k (both on a tie: the lowest index counts;
+                   // edge 2 does when neither)
 };
 
-// A face record held in registers (loaded from LDS with six 16-byte reads).
+// Staged records: a batch of up to 64 faces takes kBatchVec sixteen-byte vectors of LDS, part k
+// (of 6) of face j at vector k * kSlots + j: lane j's part k of a load is then lane-contiguous (as
+// the direct loads to LDS need it, and without bank conflicts when lane j tests face j), and one
+// face's parts are at fixed distances.  Slot 64 of every batch holds an empty record (all zero: it
+// covers no pixel), which the walks take when a batch has an odd number of faces to visit.
+constexpr int kRecParts = kRecDwords / 4;
+constexpr int kBatchVec = kRecParts * kSlots;
+
+// A face record held in registers (loaded from LDS with 16-byte reads).
 struct Rec {
   float f[kRecDwords];
 };
 
 __device__ __forceinline__ void load_rec(const float4* srec, int j, Rec& r) {
 #pragma unroll
-  for (int i = 0; i < kRecDwords / 4; ++i) {
-    const float4 q = srec[j * 6 + i];
+  for (int i = 0; i < kRecParts; ++i) {
+    const float4 q = srec[i * kSlots + j];
     r.f[4 * i] = q.x;
     r.f[4 * i + 1] = q.y;
     r.f[4 * i + 2] = q.z;
@@ -110,8 +128,8 @@ __device__ __forceinline__ void load_rec(const float4* srec, int j, Rec& r) {
 }
 
 // Evaluates one face at face-local pixel offset (dx, dy), without branches; returns whether
-// the pixel is covered (rho > 0 and alpha > 0).  alpha and I are zero when it is not.
-// Identical instructions in the forward and backward walks, so the backward recomputes
+// the pixel is covered (alpha > 0: rho <= 0 clamps to a window value of 0, and a NaN clamps to 0
+// too).  Identical instructions in the forward and backward walks, so the backward recomputes
 // alpha bit for bit.
 template <int SM>
 __device__ __forceinline__ bool eval_face(const Rec& rc, float dx, float dy, float sigma, PixelEval& e) {
@@ -119,14 +137,12 @@ __device__ __forceinline__ bool eval_face(const Rec& rc, float dx, float dy, flo
   const float E0 = fmaf(r[kRecEdge + 0], dx, fmaf(r[kRecEdge + 1], dy, r[kRecEdge + 2]));
   const float E1 = fmaf(r[kRecEdge + 3], dx, fmaf(r[kRecEdge + 4], dy, r[kRecEdge + 5]));
   const float E2 = fmaf(r[kRecEdge + 6], dx, fmaf(r[kRecEdge + 7], dy, r[kRecEdge + 8]));
-  e.k0 = E0 <= E1 && E0 <= E2;
-  e.k1 = !e.k0 && E1 <= E2;
   e.rho = fminf(E0, fminf(E1, E2));
-  const float I = e.rho >= 1.f ? 1.f : window_pow<SM>(e.rho, face_sigma<SM>(r, sigma));   // meaningless when rho <= 0
-  const float alpha = r[kRecOpa] * I;
-  const bool cov = e.rho > 0.f && alpha > 0.f;
-  e.I = cov ? I : 0.f;
-  e.alpha = cov ? alpha : 0.f;
+  e.k0 = E0 == e.rho;
+  e.k1 = E1 == e.rho;
+  e.I = window_pow<SM>(__builtin_amdgcn_fmed3f(e.rho, 0.f, 1.f), face_sigma<SM>(r, sigma));
+  e.alpha = r[kRecOpa] * e.I;
+  const bool cov = e.alpha > 0.f;
   e.c0 = fmaf(r[kRecCol + 0], dx, fmaf(r[kRecCol + 1], dy, r[kRecCol + 2]));
   e.c1 = fmaf(r[kRecCol + 3], dx, fmaf(r[kRecCol + 4], dy, r[kRecCol + 5]));
   e.c2 = fmaf(r[kRecCol + 6], dx, fmaf(r[kRecCol + 7], dy, r[kRecCol + 8]));
@@ -174,6 +190,13 @@ __device__ __forceinline__ void tile_ctx(const ViewTable& vt, const uint32_t* __
   c.end = ranges[2 * tile + 1];
 }
 
+// Sixteen bytes from memory to LDS without a register: lane l's land at dst + l (dst is the same
+// for the whole wave).
+__device__ __forceinline__ void load_lds16(const float4* src, float4* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
 // Makes this wave's LDS stores visible to its own later loads from other lanes.
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -181,55 +204,71 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Two ways to stage the records of pair positions [b0, b0 + n), n <= kBatch, into LDS:
-//  * cooperative (COOP): the four waves of the workgroup load one shared copy, with a barrier
-//    before and after, so all waves walk the batches in step (one copy of the records per
-//    tile is read from the caches);
-//  * per wave: each wave loads its own copy into its own LDS area and walks the list at its
-//    own pace (no barriers; four copies are read).
-// Which one is faster depends on how often the caches already hold the records.
-// Cooperative kernels always run kBlock threads; the staging loops below stride by kBlock, so
-// a span of any length up to kSpan is staged completely (every entry's face id and record).
-static_assert(kSpan % kBatch == 0 && kSpan >= kBatch, "a staged span is walked as whole 64-face batches");
-static_assert(kSepSpan % kBatch == 0 && kSepSpan >= kBatch && kSepSpan <= kSpan, "as kSpan");
-static_assert(kSpan * (6 * sizeof(float4) + sizeof(uint32_t)) <= 48 * 1024, "a staged span fits the LDS budget");
-static_assert(kWaves * kWave == kBlock && kWaves == 4, "one wave per 8x8 quadrant of a 16x16 tile");
-static_assert(kGradDwords == 20, "normal channels: record terms in slots 0-19 of the 24-value wave sum");
-static_assert(kWaves == kTileQuads, "normal-loss sums: one slot per wave of a tile");
-__device__ __forceinline__ void stage_batch_block(const float* __restrict__ records, const uint64_t* __restrict__ pairs,
-                                                  uint32_t b0, int n, float4* srec, uint32_t* sface,
-                                                  const float4* __restrict__ nrm = nullptr, int64_t moff = 0,
-                                                  float4* snrm = nullptr) {
-  for (int i = threadIdx.x; i < n * 6; i += kBlock) {
-    const uint32_t face = (uint32_t)pairs[b0 + i / 6];
-    srec[i] = reinterpret_cast<const float4*>(records)[(size_t)face * 6 + i % 6];
-  }
-  for (int i = threadIdx.x; i < n; i += kBlock) {
-    const uint32_t face = (uint32_t)pairs[b0 + i];
-    sface[i] = face;
-    if (nrm) snrm[i] = nrm[(int64_t)face - moff];
-  }
+constexpr int span_batches(int span) { return span / kBatch; }
+
+// Clears the empty records of a span's batches (before the barrier that follows the staging; per
+// wave staging: the wave's own batch).  Their face ids are written with the staged ones.
+__device__ __forceinline__ void clear_empty_slots(int batches, float4* srec, float4* snrm, int tid, int nthreads) {
+  for (int i = tid; i < batches * kRecParts; i += nthreads)
+    srec[i / kRecParts * kBatchVec + i % kRecParts * kSlots + kBatch] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (snrm)
+    for (int i = tid; i < batches; i += nthreads) snrm[i * kSlots + kBatch] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// Per-wave staging: lane l reads the face id of entry l; the 6 n sixteen-byte pieces are then
-// loaded by the lanes in turn (piece i by lane i % 64, face id taken from lane i / 6).  With
-// the normal channels, lane l also stages the normal of face l into snrm.
+// Two ways to stage the records of pair positions [b0, b0 + n) into LDS:
+//  * cooperative (COOP): wave w of the workgroup stages batch w of a span of up to four batches,
+//    with a barrier before and after, so all waves walk the batches in step (one copy of the
+//    records per tile is read from the caches);
+//  * per wave: each wave stages its own copy of one batch into its own LDS area and walks the
+//    list at its own pace (no barriers; four copies are read).
+// Which one is faster depends on how often the caches already hold the records.
+static_assert(kSpan % kBatch == 0 && kSpan >= kBatch && kSpan <= kWaves * kBatch, "a span is whole batches, one per wave");
+static_assert(kSepSpan % kBatch == 0 && kSepSpan >= kBatch && kSepSpan <= kSpan, "as kSpan");
+static_assert(span_batches(kSpan) * (kBatchVec * sizeof(float4) + kSlots * sizeof(uint32_t)) <= 48 * 1024,
+              "a staged span fits the LDS budget");
+static_assert(kWaves * kWave == kBlock && kWaves == 4, "one wave per 8x8 quadrant of a 16x16 tile");
+static_assert(kGradDwords == 20, "the accumulator row that grad_lane addresses");
+static_assert(kWaves == kTileQuads, "normal-loss sums: one slot per wave of a tile");
+
+// One wave stages a batch: lane l takes face l's id, then its record in kRecParts loads that go
+// straight from memory to LDS (no registers, all in flight at once), and with the normal channels
+// its normal.  The caller waits (staged_wait) before anything reads them.
 __device__ __forceinline__ void stage_batch(const float* __restrict__ records, const uint64_t* __restrict__ pairs,
                                             uint32_t b0, int n, float4* srec, uint32_t* sface,
                                             const float4* __restrict__ nrm = nullptr, int64_t moff = 0,
                                             float4* snrm = nullptr) {
   const int lane = threadIdx.x & 63;
-  const uint32_t f = lane < n ? (uint32_t)pairs[b0 + lane] : 0u;
-  if (lane < n) sface[lane] = f;
-  if (nrm && lane < n) snrm[lane] = nrm[(int64_t)f - moff];
-  const float4* rec4 = reinterpret_cast<const float4*>(records);
+  if (lane < n) {
+    const uint32_t f = (uint32_t)pairs[b0 + lane];
+    const float4* r = reinterpret_cast<const float4*>(records) + (size_t)f * kRecParts;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    const int i = lane + 64 * k;
-    const uint32_t fi = (uint32_t)__shfl((int)f, i / 6, 64);
-    if (i < n * 6) srec[i] = rec4[(size_t)fi * 6 + i % 6];
+    for (int k = 0; k < kRecParts; ++k) load_lds16(r + k, srec + k * kSlots);
+    if (nrm) snrm[lane] = nrm[(int64_t)f - moff];
+    sface[lane] = f;
+    if (lane == 0) sface[kBatch] = f;                // the empty slot: any valid id
   }
-  wave_lds_sync();
+}
+
+// Waits for the wave's loads to LDS (no register depends on them).
+__device__ __forceinline__ void staged_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Stages a span cooperatively, or a batch by this wave alone, and makes it visible to its readers.
+template <int SM, bool COOP>
+__device__ __forceinline__ void stage_span(const float* __restrict__ records, const uint64_t* __restrict__ pairs,
+                                           uint32_t b0, int n, float4* srec, uint32_t* sface, const NormalIn* nin,
+                                           int view, float4* snrm) {
+  const int w = COOP ? uniform_int((int)(threadIdx.x >> 6)) : 0;
+  const int nb = min(n - w * kBatch, kBatch);
+  if (nb > 0) {
+    if constexpr (normal_mode<SM>())
+      stage_batch(records, pairs, b0 + w * kBatch, nb, srec + w * kBatchVec, sface + w * kSlots, nin->nrm,
+                  (int64_t)view * nin->M, snrm + w * kSlots);
+    else
+      stage_batch(records, pairs, b0 + w * kBatch, nb, srec + w * kBatchVec, sface + w * kSlots);
+  }
+  staged_wait();
+  if constexpr (COOP) __syncthreads();
+  else wave_lds_sync();
 }
 
 // Faces of the staged batch that can cover a pixel of this wave's 8x8 quadrant: lane j tests
@@ -241,14 +280,27 @@ __device__ __forceinline__ void stage_batch(const float* __restrict__ records, c
 // the magnitude of the terms) exceeds the FP32 rounding of both evaluations.
 // Perspective-correct records do not hold the rectangle's end: the edge test then runs over
 // the whole quadrant (still conservative).
+__device__ __forceinline__ void load_edges(const float4* srec, int j, float (&r)[12]) {
+  static_assert(kRecEdge == 0, "the edge functions are the record's first nine dwords");
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const float4 q = srec[i * kSlots + j];
+    r[4 * i] = q.x;
+    r[4 * i + 1] = q.y;
+    r[4 * i + 2] = q.z;
+    r[4 * i + 3] = q.w;
+  }
+}
+
 template <int SM>
 __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec, int n, int bx, int by) {
   const int j = threadIdx.x & 63;
   bool hit = false;
   if constexpr (persp_mode<SM>()) {
     if (j < n) {
-      const float4 rc = srec[j * 6 + kRecU0 / 4];
-      const float* r = reinterpret_cast<const float*>(&srec[j * 6]);
+      const float4 rc = srec[kRecU0 / 4 * kSlots + j];
+      float r[12];
+      load_edges(srec, j, r);
       const float dxl = (float)bx - rc.x, dxh = (float)(bx + 7) - rc.x;
       const float dyl = (float)by - rc.y, dyh = (float)(by + 7) - rc.y;
       const float mx = fmaxf(fabsf(dxl), fabsf(dxh)), my = fmaxf(fabsf(dyl), fabsf(dyh));
@@ -265,13 +317,14 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
     return ballot(hit);
   }
   if (j < n) {
-    const float4 rc = srec[j * 6 + kRecU0 / 4];
+    const float4 rc = srec[kRecU0 / 4 * kSlots + j];
     const int u1v1 = __float_as_int(rc.z);
     const int u0 = (int)rc.x, v0 = (int)rc.y, u1 = u1v1 & 0xffff, v1 = u1v1 >> 16;
     const int xl = max(bx, u0), xh = min(bx + 7, u1), yl = max(by, v0), yh = min(by + 7, v1);
     hit = xl <= xh && yl <= yh;
     if (hit) {
-      const float* r = reinterpret_cast<const float*>(&srec[j * 6]);
+      float r[12];
+      load_edges(srec, j, r);
       const float dxl = (float)(xl - u0), dxh = (float)(xh - u0), dyl = (float)(yl - v0), dyh = (float)(yh - v0);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -290,6 +343,7 @@ struct FwdState {
   float T, C0, C1, C2, D, Tb;
   float N0, N1, N2;        // composited world normal (normal channels)
   int last;
+  uint32_t staged;         // cooperative staging: first list position of the span left in LDS
 };
 
 // A pixel blends faces while its transmittance is at least t_min and positive.  T never
@@ -299,9 +353,26 @@ struct FwdState {
 // only for t_min = 0 at a subnormal T, where nothing visible is left to blend.
 __device__ __forceinline__ bool live(float T, float t_min) { return T >= fmaxf(t_min, 1.17549435e-38f); }
 
+// Removes the lowest (highest) set bit from a batch's mask and returns its index; kBatch, the
+// empty slot, when there is none (the scalar find-bit instructions return -1 for 0).
+__device__ __forceinline__ int first_bit(unsigned long long& mask) {
+  int j;
+  asm("s_ff1_i32_b64 %0, %1\n\ts_bitset0_b64 %1, %0" : "=&s"(j), "+s"(mask));
+  return (int)min((unsigned)j, (unsigned)kBatch);
+}
+
+__device__ __forceinline__ int last_bit(unsigned long long& mask) {
+  int f;
+  asm("s_flbit_i32_b64 %0, %1\n\ts_sub_u32 %0, 63, %0\n\ts_bitset0_b64 %1, %0" : "=&s"(f), "+s"(mask) : : "scc");
+  return f;                                   // 64 for an empty mask
+}
+
 // Front-to-back walk over the tile list (eq. 4).  A pixel stops after the face that takes
 // its transmittance below t_min.  Records each pixel's last blended face and the
-// transmittance just before it.
+// transmittance just before it.  The faces of a batch's mask are taken two per round, and each
+// record is loaded from LDS a face ahead, while the other one of the pair is evaluated and
+// blended: a wave alone issues one instruction in about five cycles and waits 130 for a record,
+// and the waves of the longest tiles bound the kernel.
 template <int SM, bool COOP, int SPAN = kSpan>
 __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __restrict__ records,
                                              const uint64_t* __restrict__ pairs, float sigma, float t_min,
@@ -310,41 +381,31 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
   s.T = c.inside ? 1.f : 0.f;
   s.C0 = s.C1 = s.C2 = s.D = 0.f; s.Tb = 1.f; s.last = -1;
   s.N0 = s.N1 = s.N2 = 0.f;
+  s.staged = ~0u;
   const float dxb = (float)c.px, dyb = (float)c.py;
   constexpr int kStage = COOP ? SPAN : kBatch;      // faces staged at once
   for (uint32_t s0 = c.start; s0 < c.end; s0 += kStage) {
     const int ns = (int)min((uint32_t)kStage, c.end - s0);
     if constexpr (COOP) {
       if (__syncthreads_count(live(s.T, t_min)) == 0) break;
-      if constexpr (normal_mode<SM>())
-        stage_batch_block(records, pairs, s0, ns, srec, sface, nin->nrm, (int64_t)c.view * nin->M, snrm);
-      else
-        stage_batch_block(records, pairs, s0, ns, srec, sface);
-      __syncthreads();
     } else {
       if (ballot(live(s.T, t_min)) == 0) break;
-      if constexpr (normal_mode<SM>())
-        stage_batch(records, pairs, s0, ns, srec, sface, nin->nrm, (int64_t)c.view * nin->M, snrm);
-      else
-        stage_batch(records, pairs, s0, ns, srec, sface);
     }
+    stage_span<SM, COOP>(records, pairs, s0, ns, srec, sface, nin, c.view, snrm);
+    s.staged = s0;
     for (int h = 0; h < ns; h += kBatch) {
     bool lv = live(s.T, t_min);         // this lane still blends (carried across the visits)
     if (ballot(lv) == 0) break;
     const int n = min(kBatch, ns - h);
     const uint32_t b0 = s0 + (uint32_t)h;
-    const float4* sr = srec + h * 6;
+    const float4* sr = srec + h / kBatch * kBatchVec;
+    const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
     unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by);
-    while (mask) {
-      const int j = __builtin_ctzll(mask);
-      mask &= mask - 1;
-      Rec rc;
-      load_rec(sr, j, rc);
+    if (mask == 0ull) continue;
+    auto visit = [&](const Rec& rc, int j) {
       PixelEval e;
-      const float dx = dxb - rc.f[kRecU0];
-      const float dy = dyb - rc.f[kRecV0];
       // stopping also at T == 0 means the backward never divides by 1 - alpha = 0
-      const bool act = eval_face<SM>(rc, dx, dy, sigma, e) && lv;
+      const bool act = eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e) && lv;
       // lanes that do not blend this face keep their state: alpha 0 gives weight 0 and T * 1
       const float a = act ? e.alpha : 0.f;
       const float w = a * s.T;
@@ -353,7 +414,7 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
       s.C2 = fmaf(e.c2, w, s.C2);
       s.D = fmaf(e.zp, w, s.D);
       if constexpr (normal_mode<SM>()) {
-        const float4 nf = snrm[h + j];
+        const float4 nf = sn[j];
         s.N0 = fmaf(nf.x, w, s.N0);
         s.N1 = fmaf(nf.y, w, s.N1);
         s.N2 = fmaf(nf.z, w, s.N2);
@@ -362,7 +423,25 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
       s.last = act ? (int)(b0 + j) : s.last;
       s.T = s.T * (1.f - a);
       lv = live(s.T, t_min);
-      if (ballot(lv) == 0) break;
+    };
+    int j0 = first_bit(mask);
+    int j1 = first_bit(mask);
+    Rec r0, r1;
+    load_rec(sr, j0, r0);
+    load_rec(sr, j1, r1);
+    for (;;) {
+      visit(r0, j0);
+      j0 = first_bit(mask);
+      __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
+      load_rec(sr, j0, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      visit(r1, j1);
+      j1 = first_bit(mask);
+      __builtin_amdgcn_sched_barrier(0);
+      load_rec(sr, j1, r1);
+      __builtin_amdgcn_sched_barrier(0);
+      const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
+      if (done) break;
     }
     }
   }
@@ -373,6 +452,126 @@ struct PixGrad {
   float g0, g1, g2, gd, gt;
   float gn0 = 0.f, gn1 = 0.f, gn2 = 0.f;
 };
+
+// One face's gradient terms at a pixel, as the wave sums take them: p0 the terms that also have
+// a moment with respect to dy (the three edges' dL/dE_k, the three colours' dL/dc_ch, then
+// dL/do_F without one, and the z_F term or, perspective-correct, the W plane's dL/dW with one),
+// p1 the moments with respect to dx (edges, colours, then the W plane's or the term of the face's
+// own exponent), p2 the normal channels.
+template <int SM> constexpr int p1_terms() { return persp_mode<SM>() || exp_mode<SM>() == 4 ? 7 : 6; }
+
+template <int SM>
+struct FaceTerms {
+  float p0[8], p1[p1_terms<SM>()], p2[3];
+};
+
+// Sums of two faces' terms over the wave; lane l holds one total (which one: grad_lane).
+//   sum over x: P0, P1 (P2) of each face (sum_face_x); Q0 = P0 dy of the lane's row of pixels;
+//   bit 3: U = (P0, P1) of each face, V = (Q0 of face 0, Q0 of face 1), R = (P2, P2);
+//   bit 5: X = (U of face 0, U of face 1), Y = V (with the normals: (V, R)); bit 4: (X, Y).
+struct FaceSums {
+  float p0, p1, p2, q0;
+};
+
+template <int SM>
+__device__ __forceinline__ FaceSums sum_face_x(FaceTerms<SM>& ft, float dy) {
+  sum_x(ft.p0, ft.p1);
+  if constexpr (normal_mode<SM>()) sum_x(ft.p2);
+  return FaceSums{ft.p0[0], ft.p1[0], normal_mode<SM>() ? ft.p2[0] : 0.f, ft.p0[0] * dy};
+}
+
+template <int SM>
+__device__ __forceinline__ float sum_faces(FaceSums& f0, FaceSums& f1) {
+  pair_bit3(f0.p0, f0.p1, f1.p0, f1.p1, f0.q0, f1.q0);
+  const float x = sum_bit5(f0.p0, f1.p0);
+  float y;
+  if constexpr (normal_mode<SM>()) {
+    pair_bit3(f0.p2, f1.p2);
+    y = sum_bit5(f0.q0, f0.p2);
+  } else {
+    y = sum_bit5(f0.q0, f0.q0);
+  }
+  float out = sum_bit4(x, y);
+  // keeps the sums in this (full-wave) part of the code instead of letting them move into a
+  // caller's branch on the lane
+  asm volatile("" : "+v"(out));
+  return out;
+}
+
+// Where this lane's total of sum_faces goes: which face of the pair (-1: the lane holds none),
+// and the address base + id * stride of its accumulator (acc: the gradient accumulator, whose
+// element type may be double).
+struct GradLane {
+  int face;
+  uint32_t stride;
+  char* base;
+  bool acc;
+};
+
+template <int SM>
+__device__ __forceinline__ GradLane grad_lane(acc_t* grad_acc, float* sig_acc, float* persp_acc, float* gacc,
+                                              int64_t moff) {
+  const int lane = threadIdx.x & 63, x = lane & 7;
+  const bool b3 = lane & 8, b4 = lane & 16, b5 = lane & 32;
+  int face = -1, k = -1, where = 0;      // where: 0 gradient accumulator, 1 exponent, 2 W plane, 3 normal
+  if (!b4) {
+    face = b5 ? 1 : 0;
+    if (!b3) {
+      const int i = sum_x_slot<8>(x);
+      k = i < 3 ? kGEdge + 3 * i + 2 : (i < 6 ? kGCol + 3 * (i - 3) + 2 : (i == 6 ? (int)kGOpa : (int)kGZ));
+    } else {
+      const int i = sum_x_slot<p1_terms<SM>()>(x);
+      if (i == 6) {
+        where = persp_mode<SM>() ? 2 : 1;
+        k = 0;
+      } else if (i >= 0) {
+        k = i < 3 ? kGEdge + 3 * i : kGCol + 3 * (i - 3);
+      }
+    }
+  } else if (!b5) {
+    face = b3 ? 1 : 0;
+    const int i = sum_x_slot<8>(x);
+    if (i < 6) {
+      k = i < 3 ? kGEdge + 3 * i + 1 : kGCol + 3 * (i - 3) + 1;
+    } else if (persp_mode<SM>() && i == 7) {
+      where = 2;
+      k = 1;
+    }
+  } else if (normal_mode<SM>()) {
+    face = b3 ? 1 : 0;
+    where = 3;
+    k = sum_x_slot<3>(x);
+  }
+  GradLane g;
+  g.face = k >= 0 ? face : -1;
+  g.acc = where == 0;
+  const int kk = k >= 0 ? k : 0;
+  if (where == 0) {
+    g.stride = kGradDwords * sizeof(acc_t);
+    g.base = reinterpret_cast<char*>(grad_acc + kk);
+  } else if (where == 1) {
+    g.stride = sizeof(float);
+    g.base = reinterpret_cast<char*>(sig_acc);
+  } else if (where == 2) {
+    g.stride = 2 * sizeof(float);
+    g.base = reinterpret_cast<char*>(persp_acc + kk);
+  } else {
+    g.stride = sizeof(float4);
+    g.base = reinterpret_cast<char*>(gacc + kk) - moff * (int64_t)sizeof(float4);
+  }
+  return g;
+}
+
+template <int SM>
+__device__ __forceinline__ void add_total(const GradLane& gl, uint32_t g, float tot) {
+  char* p = gl.base + (uint64_t)g * gl.stride;
+  if constexpr (sizeof(acc_t) == sizeof(float)) {
+    unsafeAtomicAdd(reinterpret_cast<float*>(p), tot);
+  } else {
+    if (gl.acc) unsafeAtomicAdd(reinterpret_cast<acc_t*>(p), (acc_t)tot);
+    else unsafeAtomicAdd(reinterpret_cast<float*>(p), tot);
+  }
+}
 
 // Back-to-front walk (Sec. 3.3).  T before each face is recovered by division from the
 // transmittance before the last blended face.  What lies behind the current face, composited
@@ -386,156 +585,134 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
                                               const PixGrad& pg, float4* srec, uint32_t* sface, int* sint,
                                               acc_t* __restrict__ grad_acc, float* __restrict__ sig_acc,
                                               float* __restrict__ persp_acc, const NormalIn* nin = nullptr,
-                                              float4* snrm = nullptr) {
+                                              float4* snrm = nullptr, uint32_t staged = ~0u) {
   const int lane = threadIdx.x & 63;
   // highest list position any pixel of this wave (COOP: of the workgroup) blended
   const int wlast = uniform_int(wave_max_int(last));
+  constexpr int kStage = COOP ? SPAN : kBatch;      // faces staged at once
   int top = wlast;
-  if constexpr (COOP) {
+  if (COOP && c.end - c.start <= (uint32_t)kStage) {
+    top = (int)c.end - 1;                           // one span: staged whole, whatever was blended
+  } else if constexpr (COOP) {
     if (threadIdx.x == 0) sint[0] = -1;
     __syncthreads();
     if (lane == 0) atomicMax(&sint[0], wlast);
     __syncthreads();
     top = uniform_int(sint[0]);
   }
-  // With terms beyond the record's 20 (normal channels: 3 in slots 20-22; perspective without
-  // them: the W plane's 2 slopes in slots 20-21; per-face exponent: slot 23) all go through one
-  // 24-value transposed sum.
-  constexpr bool kWide = normal_mode<SM>() || persp_mode<SM>() || exp_mode<SM>() == 4;
-  const int k_out = kWide ? wave_sum24_slot() : wave_sum20_slot();
+  const GradLane gl = grad_lane<SM>(grad_acc, sig_acc, persp_acc,
+                                    normal_mode<SM>() ? reinterpret_cast<float*>(nin->gacc) : nullptr,
+                                    normal_mode<SM>() ? (int64_t)c.view * nin->M : 0);
   float Tcur = Tb;
   float S = 0.f;
   const float dxb = (float)c.px, dyb = (float)c.py;
-  constexpr int kStage = COOP ? SPAN : kBatch;      // faces staged at once
-  for (int s1 = top + 1; s1 > (int)c.start; s1 -= kStage) {
-    const int s0 = max((int)c.start, s1 - kStage);
+  for (int s1 = top + 1, s0; s1 > (int)c.start; s1 = s0) {
+    // cooperative spans start where the forward's do, so that the last one it staged is still there
+    s0 = COOP ? (int)c.start + (s1 - 1 - (int)c.start) / kStage * kStage : max((int)c.start, s1 - kStage);
     const int ns = s1 - s0;
-    if constexpr (COOP) {
-      __syncthreads();
-      if constexpr (normal_mode<SM>())
-        stage_batch_block(records, pairs, (uint32_t)s0, ns, srec, sface, nin->nrm, (int64_t)c.view * nin->M, snrm);
-      else
-        stage_batch_block(records, pairs, (uint32_t)s0, ns, srec, sface);
-      __syncthreads();
-    } else {
-      if constexpr (normal_mode<SM>())
-        stage_batch(records, pairs, (uint32_t)s0, ns, srec, sface, nin->nrm, (int64_t)c.view * nin->M, snrm);
-      else
-        stage_batch(records, pairs, (uint32_t)s0, ns, srec, sface);
+    if (!COOP || (uint32_t)s0 != staged) {
+      if constexpr (COOP) __syncthreads();
+      stage_span<SM, COOP>(records, pairs, (uint32_t)s0, ns, srec, sface, nin, c.view, snrm);
     }
     for (int h = ((ns - 1) / kBatch) * kBatch; h >= 0; h -= kBatch) {
     const int b0 = s0 + h;
     const int n = min(kBatch, ns - h);
     if (b0 > wlast) continue;
-    const float4* sr = srec + h * 6;
-    const uint32_t* sf = sface + h;
+    const float4* sr = srec + h / kBatch * kBatchVec;
+    const uint32_t* sf = sface + h / kBatch * kSlots;
+    const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
     unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by);
     if (wlast - b0 < 63) mask &= (2ull << (wlast - b0)) - 1ull;     // faces after the wave's last
-    while (mask) {
-      const int j = 63 - __builtin_clzll(mask);
-      mask &= ~(1ull << j);
+    if (mask == 0ull) continue;
+    auto visit = [&](const Rec& rc, int j) -> FaceSums {
+      // Every lane evaluates the face; lanes that do not blend it (not covered, or behind their
+      // last face) get alpha 0 and zero gradient scales, so all sums need no branches.
       const int idx = b0 + j;
-      Rec rc;
-      load_rec(sr, j, rc);
-      const float* r = rc.f;
-      // Every lane evaluates the face; lanes that do not blend it (not covered, or behind
-      // their last face) get alpha = I = 0, hence zero weight and zero gradient scales, so
-      // all 20 sums need no branches.
-      const float dx = dxb - r[kRecU0];
-      const float dy = dyb - r[kRecV0];
+      const float dx = dxb - rc.f[kRecU0];
+      const float dy = dyb - rc.f[kRecV0];
       PixelEval e;
       const bool act = eval_face<SM>(rc, dx, dy, sigma, e) && (idx <= last);
+      FaceTerms<SM> ft;
       const float alpha = act ? e.alpha : 0.f;
-      const float I = act ? e.I : 0.f;
       const float om = 1.f - alpha;
-      // T before this face: the stored value at the last face, else T_after / (1 - alpha)
-      const float Tj = (idx == last) ? Tb : Tcur * __builtin_amdgcn_rcpf(om);
-      Tcur = act ? Tj : Tcur;
+      // T before this face: the stored value at the last face, else T_after / (1 - alpha), which
+      // is T_after itself where the face is not blended (rcp(1) = 1; the empty record's idx may be
+      // that of a later face)
+      const float Tj = (act && idx == last) ? Tb : Tcur * __builtin_amdgcn_rcpf(om);
+      Tcur = Tj;
       const float zf = e.zp;
       const float c0 = e.c0, c1 = e.c1, c2 = e.c2;
       const float w = alpha * Tj;
-      float acc[kWide ? 24 : kGradDwords];
       // colour plane gradients: dL/dc_ch(p) = gC_ch alpha T, and c_ch = P dx + Q dy + R
       float gc0 = pg.g0 * w, gc1 = pg.g1 * w, gc2 = pg.g2 * w;
-      float gwa = 0.f, gwb = 0.f;          // perspective-correct: the W plane's slopes
+      float gz = 0.f;
       if constexpr (persp_mode<SM>()) {
         // c_ch = N_ch / W, depth = 1 / W: dL/dN_ch = gC_ch w / W, dL/dW = -(gC.c + gD depth) w / W
-        const float gW = -(fmaf(pg.g0, c0, fmaf(pg.g1, c1, fmaf(pg.g2, c2, pg.gd * zf)))) * w * zf;
+        gz = -(fmaf(pg.g0, c0, fmaf(pg.g1, c1, fmaf(pg.g2, c2, pg.gd * zf)))) * w * zf;
         gc0 *= zf;
         gc1 *= zf;
         gc2 *= zf;
-        acc[kGWc] = gW;
-        gwa = gW * dx;
-        gwb = gW * dy;
       } else {
-        acc[kGZ] = pg.gd * w;
+        gz = pg.gd * w;
       }
-      acc[kGCol + 0] = gc0 * dx; acc[kGCol + 1] = gc0 * dy; acc[kGCol + 2] = gc0;
-      acc[kGCol + 3] = gc1 * dx; acc[kGCol + 4] = gc1 * dy; acc[kGCol + 5] = gc1;
-      acc[kGCol + 6] = gc2 * dx; acc[kGCol + 7] = gc2 * dy; acc[kGCol + 8] = gc2;
-      // dL/dalpha = T (gC.(c - B) + gD (z - BD) - gT (1 - BA)) = T (P - S); finite on every
-      // lane, and only used scaled by I or masked by act
+      // dL/dalpha = T (gC.(c - B) + gD (z - BD) - gT (1 - BA)) = T (P - S)
       float P = fmaf(pg.g0, c0, fmaf(pg.g1, c1, fmaf(pg.g2, c2, fmaf(pg.gd, zf, -pg.gt))));
-      float4 nf = make_float4(0.f, 0.f, 0.f, 0.f);
       if constexpr (normal_mode<SM>()) {
         // the face's normal is a colour constant over the face: it enters dL/dalpha like one
-        nf = snrm[h + j];
+        const float4 nf = sn[j];
         P = fmaf(pg.gn0, nf.x, fmaf(pg.gn1, nf.y, fmaf(pg.gn2, nf.z, P)));
       }
-      const float galpha = Tj * (P - S);
-      acc[kGOpa] = galpha * I;
-      const float gI = galpha * r[kRecOpa];
-      float grho = 0.f;
-      if constexpr (exp_mode<SM>() == 1) grho = (act && e.rho < 1.f) ? gI : 0.f;
-      else grho = (act && e.rho < 1.f) ? gI * face_sigma<SM>(r, sigma) * I * __builtin_amdgcn_rcpf(e.rho) : 0.f;   // sigma I / rho
-      // only the edge attaining the minimum receives the window gradient
-      const float gk[3] = {e.k0 ? grho : 0.f, e.k1 ? grho : 0.f, (e.k0 || e.k1) ? 0.f : grho};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        acc[kGEdge + 3 * k + 0] = gk[k] * dx;
-        acc[kGEdge + 3 * k + 1] = gk[k] * dy;
-        acc[kGEdge + 3 * k + 2] = gk[k];
-      }
+      const float galpha = act ? Tj * (P - S) : 0.f;
       S = fmaf(alpha, P, om * S);
-      if (ballot(act) == 0) continue;
+      const float gI = galpha * rc.f[kRecOpa];
+      float grho = 0.f;
+      if constexpr (exp_mode<SM>() == 1) grho = e.rho < 1.f ? gI : 0.f;
+      else grho = (act && e.rho < 1.f) ? gI * face_sigma<SM>(rc.f, sigma) * e.I * __builtin_amdgcn_rcpf(e.rho) : 0.f;   // sigma I / rho
+      // only the edge attaining the minimum receives the window gradient (the others' differences
+      // are exact zeros)
+      const float gk0 = e.k0 ? grho : 0.f, g12 = grho - gk0;
+      const float gk1 = e.k1 ? g12 : 0.f, gk2 = g12 - gk1;
+      float* p0 = ft.p0;
+      p0[0] = gk0; p0[1] = gk1; p0[2] = gk2;
+      p0[3] = gc0; p0[4] = gc1; p0[5] = gc2;
+      p0[6] = galpha * e.I;
+      p0[7] = gz;
+      float* p1 = ft.p1;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) p1[k] = p0[k] * dx;
+      if constexpr (persp_mode<SM>()) p1[6] = gz * dx;
       // the face's own exponent: dI/dsigma = I ln(rho) for 0 < rho < 1 (act implies rho > 0)
-      float gsig = 0.f;
       if constexpr (exp_mode<SM>() == 4)
-        gsig = (act && e.rho < 1.f) ? gI * I * (0.69314718055994531f * log2f(e.rho)) : 0.f;
-      if constexpr (kWide) {
-        if constexpr (normal_mode<SM>()) {
-          // dE/dn_F = sum over the face's pixels of gN alpha T
-          acc[20] = pg.gn0 * w;
-          acc[21] = pg.gn1 * w;
-          acc[22] = pg.gn2 * w;
-        } else {
-          acc[20] = gwa;
-          acc[21] = gwb;
-          acc[22] = 0.f;
-        }
-        acc[23] = gsig;
-        const float tot = wave_sum24(acc);
-        if (k_out >= 0 && k_out < kGradDwords) {
-          unsafeAtomicAdd(&grad_acc[(size_t)sf[j] * kGradDwords + k_out], (acc_t)tot);
-        } else if (normal_mode<SM>() && k_out >= kGradDwords && k_out < 23) {
-          float* ga = reinterpret_cast<float*>(nin->gacc + ((int64_t)sf[j] - (int64_t)c.view * nin->M));
-          unsafeAtomicAdd(&ga[k_out - kGradDwords], tot);
-        } else if (!normal_mode<SM>() && persp_mode<SM>() && (k_out == 20 || k_out == 21)) {
-          unsafeAtomicAdd(&persp_acc[2 * (size_t)sf[j] + (k_out - 20)], tot);
-        } else if (exp_mode<SM>() == 4 && k_out == 23) {
-          unsafeAtomicAdd(&sig_acc[sf[j]], tot);
-        }
-        if constexpr (normal_mode<SM>() && persp_mode<SM>()) {
-          const float ta = wave_sum(gwa), tb = wave_sum(gwb);
-          if (lane == 0) {
-            unsafeAtomicAdd(&persp_acc[2 * (size_t)sf[j]], ta);
-            unsafeAtomicAdd(&persp_acc[2 * (size_t)sf[j] + 1], tb);
-          }
-        }
-      } else {
-        const float tot = wave_sum20(acc);
-        if (k_out >= 0) unsafeAtomicAdd(&grad_acc[(size_t)sf[j] * kGradDwords + k_out], (acc_t)tot);
+        p1[6] = (act && e.rho < 1.f) ? gI * e.I * (0.69314718055994531f * log2f(e.rho)) : 0.f;
+      if constexpr (normal_mode<SM>()) {
+        // dE/dn_F = sum over the face's pixels of gN alpha T
+        ft.p2[0] = pg.gn0 * w;
+        ft.p2[1] = pg.gn1 * w;
+        ft.p2[2] = pg.gn2 * w;
       }
+      return sum_face_x<SM>(ft, dy);
+    };
+    int j0 = last_bit(mask), j1 = last_bit(mask);
+    Rec r0, r1;
+    load_rec(sr, j0, r0);
+    load_rec(sr, j1, r1);
+    for (;;) {
+      // the id that this lane's total goes to (its load is as old as the sums when it is used)
+      const uint32_t id = sf[gl.face > 0 ? j1 : j0];
+      FaceSums f0 = visit(r0, j0);
+      j0 = last_bit(mask);
+      __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
+      load_rec(sr, j0, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      FaceSums f1 = visit(r1, j1);
+      j1 = last_bit(mask);
+      __builtin_amdgcn_sched_barrier(0);
+      load_rec(sr, j1, r1);
+      __builtin_amdgcn_sched_barrier(0);
+      const float tot = sum_faces<SM>(f0, f1);
+      // one atomic per lane that holds a total (0 for the empty record)
+      if (gl.face >= 0) add_total<SM>(gl, id, tot);
+      if (j0 == kBatch) break;
     }
     }
   }
@@ -546,7 +723,7 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
 // COOP: the tile's list is staged cooperatively (one shared copy per workgroup, the four
 // quadrant waves in step), else per wave (four copies, each wave at its own pace).
 template <int SM, bool COOP>
-__global__ __launch_bounds__(kBlock) void k_blend_fwd(ViewTable vt, const float* __restrict__ records,
+__global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const float* __restrict__ records,
                                                       const uint64_t* __restrict__ pairs,
                                                       const uint32_t* __restrict__ ranges, float sigma, float t_min,
                                                       float* __restrict__ color, float* __restrict__ depth,
@@ -560,14 +737,16 @@ __global__ __launch_bounds__(kBlock) void k_blend_fwd(ViewTable vt, const float*
   tile_ctx(vt, ranges, tile, wv, c);
   FwdState s;
   if constexpr (COOP) {
-    __shared__ float4 srec[kSepSpan * 6];
-    __shared__ uint32_t sface[kSepSpan];
-    __shared__ float4 snrm[normal_mode<SM>() ? kSepSpan : 1];
+    __shared__ float4 srec[span_batches(kSepSpan) * kBatchVec];
+    __shared__ uint32_t sface[span_batches(kSepSpan) * kSlots];
+    __shared__ float4 snrm[normal_mode<SM>() ? span_batches(kSepSpan) * kSlots : 1];
+    clear_empty_slots(span_batches(kSepSpan), srec, normal_mode<SM>() ? snrm : nullptr, threadIdx.x, kBlock);
     forward_walk<SM, true, kSepSpan>(c, records, pairs, sigma, t_min, srec, sface, s, &nin, snrm);
   } else {
-    __shared__ float4 srec[kWaves][kBatch * 6];
-    __shared__ uint32_t sface[kWaves][kBatch];
-    __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kBatch : 1];
+    __shared__ float4 srec[kWaves][kBatchVec];
+    __shared__ uint32_t sface[kWaves][kSlots];
+    __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kSlots : 1];
+    clear_empty_slots(1, srec[wv], normal_mode<SM>() ? snrm[wv] : nullptr, threadIdx.x & 63, kWave);
     forward_walk<SM, false>(c, records, pairs, sigma, t_min, srec[wv], sface[wv], s, &nin, snrm[wv]);
   }
   const int64_t hw = (int64_t)c.vd.width * c.vd.height;
@@ -615,7 +794,7 @@ __global__ __launch_bounds__(kBlock) void k_blend_fwd(ViewTable vt, const float*
 }
 
 template <int SM, bool COOP>
-__global__ __launch_bounds__(kBlock) void k_blend_bwd(ViewTable vt, const float* __restrict__ records,
+__global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const float* __restrict__ records,
                                                       const uint64_t* __restrict__ pairs,
                                                       const uint32_t* __restrict__ ranges, float sigma,
                                                       const int* __restrict__ n_last, const float* __restrict__ t_last,
@@ -662,16 +841,18 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(ViewTable vt, const float*
     }
   }
   if constexpr (COOP) {
-    __shared__ float4 srec[kSepSpan * 6];
-    __shared__ uint32_t sface[kSepSpan];
-    __shared__ float4 snrm[normal_mode<SM>() ? kSepSpan : 1];
+    __shared__ float4 srec[span_batches(kSepSpan) * kBatchVec];
+    __shared__ uint32_t sface[span_batches(kSepSpan) * kSlots];
+    __shared__ float4 snrm[normal_mode<SM>() ? span_batches(kSepSpan) * kSlots : 1];
+    clear_empty_slots(span_batches(kSepSpan), srec, normal_mode<SM>() ? snrm : nullptr, threadIdx.x, kBlock);
     __shared__ int sint[4];
     backward_walk<SM, true, kSepSpan>(c, records, pairs, sigma, last, Tb, pg, srec, sface, sint, grad_acc, sig_acc,
                                       persp_acc, &nin, snrm);
   } else {
-    __shared__ float4 srec[kWaves][kBatch * 6];
-    __shared__ uint32_t sface[kWaves][kBatch];
-    __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kBatch : 1];
+    __shared__ float4 srec[kWaves][kBatchVec];
+    __shared__ uint32_t sface[kWaves][kSlots];
+    __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kSlots : 1];
+    clear_empty_slots(1, srec[wv], normal_mode<SM>() ? snrm[wv] : nullptr, threadIdx.x & 63, kWave);
     backward_walk<SM, false>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc, sig_acc,
                              persp_acc, &nin, snrm[wv]);
   }
@@ -680,8 +861,9 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(ViewTable vt, const float*
 // Fused training kernel: forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
 // images and runs in tsr_ssim.hip between a separate forward and backward), backward
 // walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant).
+// Five workgroups per CU (96 registers a lane): the records of two faces in flight.
 template <int SM>
-__global__ __launch_bounds__(kBlock) void k_train_fused(ViewTable vt, const float* __restrict__ records,
+__global__ __launch_bounds__(kBlock, 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
                                                         const uint64_t* __restrict__ pairs,
                                                         const uint32_t* __restrict__ ranges, float sigma, float t_min,
                                                         float w_color, float w_depth,
@@ -693,11 +875,12 @@ __global__ __launch_bounds__(kBlock) void k_train_fused(ViewTable vt, const floa
                                                         const int* __restrict__ order, int* __restrict__ queue,
                                                         int persistent) {
   // the four waves stage each span together (one copy of the records per tile)
-  __shared__ float4 srec[kSpan * 6];
-  __shared__ uint32_t sface[kSpan];
+  __shared__ float4 srec[span_batches(kSpan) * kBatchVec];
+  __shared__ uint32_t sface[span_batches(kSpan) * kSlots];
   __shared__ int s_item;
   __shared__ int sint[4];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  clear_empty_slots(span_batches(kSpan), srec, nullptr, threadIdx.x, kBlock);
   int round = 0;
   for (;;) {
     int tile;
@@ -726,17 +909,24 @@ __global__ __launch_bounds__(kBlock) void k_train_fused(ViewTable vt, const floa
     if (c.end - c.start > TSR_PRIO_LONG) __builtin_amdgcn_s_setprio(2);
     else __builtin_amdgcn_s_setprio(0);
 #endif
+    // the pixel's targets are loaded ahead of the walk, which hides their latency
+    const int64_t hw = (int64_t)c.vd.width * c.vd.height;
+    const int64_t off = (int64_t)c.py * c.vd.width + c.px;
+    float t0 = 0.f, t1 = 0.f, t2 = 0.f, td = 0.f;
+    if (c.inside) {
+      const float* tc = tcolor + 3 * c.vd.pix_off + off;
+      t0 = tc[0];
+      t1 = tc[hw];
+      t2 = tc[2 * hw];
+      td = tdepth[c.pix];
+    }
     FwdState s;
     forward_walk<SM, true>(c, records, pairs, sigma, t_min, srec, sface, s);
     PixGrad pg{0.f, 0.f, 0.f, 0.f, 0.f};
     float lpix = 0.f;
     if (c.inside) {
-      const int64_t hw = (int64_t)c.vd.width * c.vd.height;
-      const int64_t off = (int64_t)c.py * c.vd.width + c.px;
       const float inv_c = w_color / (3.f * (float)hw), inv_d = w_depth / (float)hw;
-      const float* tc = tcolor + 3 * c.vd.pix_off + off;
-      const float r0 = s.C0 - tc[0], r1 = s.C1 - tc[hw], r2 = s.C2 - tc[2 * hw];
-      const float td = tdepth[c.pix];
+      const float r0 = s.C0 - t0, r1 = s.C1 - t1, r2 = s.C2 - t2;
       const float rd = s.D - td;
       const float md = td > 0.f ? 1.f : 0.f;
       pg.g0 = inv_c * (float)((r0 > 0.f) - (r0 < 0.f));
@@ -759,7 +949,7 @@ __global__ __launch_bounds__(kBlock) void k_train_fused(ViewTable vt, const floa
       if (lane == 0) loss_part[kWaves * tile + quad] = ws;
     }
     backward_walk<SM, true>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
-                            persp_acc);
+                            persp_acc, nullptr, nullptr, s.staged);
     if (!persistent) break;
   }
 }
@@ -1407,20 +1597,20 @@ static bool separate_coop(const ViewTable& vt) { return vt.n_views > 1; }
 // decisions as the forward pass (one wave per 8x8 quadrant, per-wave staging).  Each pixel
 // counts 1 for the coverage of the face with the largest blending weight alpha T along its
 // ray (the first in depth order on ties), summed per wave before the atomics; a face blended
-// at any pixel is marked visible (one store per wave and face visit, from the first lane that
-// blends it).
+// at any pixel is marked visible (lane j stores for face j of the batch).
 template <int SM>
 __global__ __launch_bounds__(kBlock) void k_face_stats(ViewTable vt, const float* __restrict__ records,
                                                        const uint64_t* __restrict__ pairs,
                                                        const uint32_t* __restrict__ ranges, float sigma, float t_min,
                                                        uint32_t* __restrict__ coverage, uint32_t* __restrict__ visible,
                                                        const int* __restrict__ order) {
-  __shared__ float4 srec[kWaves][kBatch * 6];
-  __shared__ uint32_t sface[kWaves][kBatch];
+  __shared__ float4 srec[kWaves][kBatchVec];
+  __shared__ uint32_t sface[kWaves][kSlots];
   const int wv = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int tile = tile_of_block_ordered(vt.n_tiles, order);
   if (tile < 0) return;
+  clear_empty_slots(1, srec[wv], nullptr, lane, kWave);
   TileCtx c;
   tile_ctx(vt, ranges, tile, wv, c);
   float T = c.inside ? 1.f : 0.f, best_w = 0.f;
@@ -1429,36 +1619,50 @@ __global__ __launch_bounds__(kBlock) void k_face_stats(ViewTable vt, const float
   for (uint32_t b0 = c.start; b0 < c.end; b0 += kBatch) {
     if (ballot(live(T, t_min)) == 0) break;
     const int n = (int)min((uint32_t)kBatch, c.end - b0);
-    stage_batch(records, pairs, b0, n, srec[wv], sface[wv]);
+    stage_span<SM, false>(records, pairs, b0, n, srec[wv], sface[wv], nullptr, 0, nullptr);
     unsigned long long mask = batch_hit_mask<SM>(srec[wv], n, c.bx, c.by);
+    if (mask == 0ull) continue;
     bool lv = live(T, t_min);
-    while (mask) {
-      const int j = __builtin_ctzll(mask);
-      mask &= mask - 1;
-      Rec rc;
-      load_rec(srec[wv], j, rc);
+    unsigned long long seen = 0ull;
+    auto visit = [&](const Rec& rc, int j) {
       PixelEval e;
-      const float dx = dxb - rc.f[kRecU0];
-      const float dy = dyb - rc.f[kRecV0];
-      const bool act = eval_face<SM>(rc, dx, dy, sigma, e) && lv;
+      const bool act = eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e) && lv;
       const float a = act ? e.alpha : 0.f;
       const float w = a * T;
-      const uint32_t g = sface[wv][j];
-      if (act && w > best_w) {
-        best_w = w;
-        best = (int)g;
-      }
-      const unsigned long long bm = ballot(act);
-      if (visible && bm != 0ull && lane == __builtin_ctzll(bm)) visible[g] = 1u;
+      const bool top = act && w > best_w;
+      best_w = top ? w : best_w;
+      best = top ? (int)b0 + j : best;
+      // visible faces of the batch, one bit each (the empty record is never blended)
+      seen |= ballot(act) != 0ull ? 1ull << (j & 63) : 0ull;
       T = T * (1.f - a);
       lv = live(T, t_min);
-      if (ballot(lv) == 0) break;
+    };
+    // two faces per round, each record loaded a face ahead (as forward_walk)
+    int j0 = first_bit(mask), j1 = first_bit(mask);
+    Rec r0, r1;
+    load_rec(srec[wv], j0, r0);
+    load_rec(srec[wv], j1, r1);
+    for (;;) {
+      visit(r0, j0);
+      j0 = first_bit(mask);
+      __builtin_amdgcn_sched_barrier(0);
+      load_rec(srec[wv], j0, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      visit(r1, j1);
+      j1 = first_bit(mask);
+      __builtin_amdgcn_sched_barrier(0);
+      load_rec(srec[wv], j1, r1);
+      __builtin_amdgcn_sched_barrier(0);
+      const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
+      if (done) break;
     }
+    if (visible && ((seen >> lane) & 1ull)) visible[sface[wv][lane]] = 1u;
   }
   if (coverage) {
     // one atomic per distinct dominant face of the wave, adding its number of pixels (a large
     // face dominates many pixels, and atomics on one address serialise)
     bool pending = best >= 0;
+    if (pending) best = (int)(uint32_t)pairs[best];          // list position -> face id
     for (;;) {
       const unsigned long long pm = ballot(pending);
       if (pm == 0ull) break;

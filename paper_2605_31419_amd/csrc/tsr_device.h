@@ -70,11 +70,16 @@ struct ViewTable {
   int32_t pad;
 };
 
+// View of a global tile id.  Unused table entries hold a tile_off above every tile id, so the
+// entries are compared eight at a time (their scalar loads overlap).
 __device__ __forceinline__ int view_of_tile(const ViewTable& vt, int tile) {
+  if (vt.n_views == 1) return 0;
   int v = 0;
-  for (int i = 1; i < vt.n_views; ++i)
-    if (tile >= vt.v[i].tile_off) v = i;
-  return v;
+  for (int i0 = 0; i0 < vt.n_views; i0 += 8) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v += tile >= vt.v[i0 + i].tile_off ? 1 : 0;
+  }
+  return v - 1;
 }
 
 // ---------------------------------------------------------------------------- wave64 DPP
@@ -98,111 +103,169 @@ __device__ __forceinline__ float wave_sum(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to_lane63(v)), 63));
 }
 
-// Wave totals of 20 per-lane values with a transposing butterfly: at each level a pair of
-// vectors (x, y) becomes one, the lanes on one side of the level's partner bit keeping x summed
-// with their partner lane and the others keeping y.
-//   v_permlane32_swap (partner l ^ 32): 20 -> 10 vectors;
-//   v_permlane16_swap (rows 0 <-> 1, 2 <-> 3): 10 -> 5; row r now holds value 4 j + {0, 2, 1, 3}[r]
-//     of vector j, summed over the four rows;
-//   inside each row, bit 3 (partner l ^ 8, row_ror:8): 5 -> 3 (the odd vector is summed over
-//     the pair); bit 2 (partner l ^ 7, row_half_mirror): 3 -> 2; bits 1 and 0 (quad_perm):
-//     both summed.
-// The partners span all 64 lanes, so every kept value is a wave total.  The paired vector's
-// totals (16 values) are read on lanes x = 0, 4, 8, 12 of each row, the odd vector's (the other
-// 4, the same on every lane of a row) on lane x = 1: the result is value wave_sum20_slot() on
-// the 20 lanes where that is not -1.  Every lane must be active.
-__device__ __forceinline__ int wave_sum20_slot() {
-  const int r = (threadIdx.x & 63) >> 4, x = threadIdx.x & 15;
-  const int rmap = r == 0 ? 0 : (r == 1 ? 2 : (r == 2 ? 1 : 3));
-  return (x & 3) == 0 ? 4 * (2 * ((x >> 2) & 1) + ((x >> 3) & 1)) + rmap : (x == 1 ? 16 + rmap : -1);
+// Sums of per-pixel gradient terms over the 8x8 pixels of a wave (lane = 8 y + x), for two faces
+// at a time.  The sums are taken in the order x, then y, so that a term's moment with respect to
+// y is formed after its sum over x (one product per eight pixels); every level is a transposing
+// butterfly: a pair of vectors (a, b) becomes one, the lanes on one side of the level's partner
+// bit keeping a summed with their partner and the others keeping b.
+//
+// On gfx950 a wave64 v_permlane*_swap takes 8 cycles of a SIMD, a DPP add 4, a plain add or
+// multiply 2 (4 when nothing of the other kind can issue beside it).  Lane bits 2 and 3 are
+// therefore reduced by pairs of DPP adds that write only the banks of their side (a bank is four
+// lanes; no select needed), bits 1 and 0 by quad permutes and a select, and only the last two
+// levels, on the three or four vectors that are left of two faces, use swaps.
+//
+// The x levels are one asm block per face: the compiler cannot fold a masked DPP move into an add,
+// and inside a block the two wait states between a write and a DPP read of the same register are
+// kept by the order of the instructions (the hazard tables do not look inside asm: the leading
+// s_nop covers what was written just before).
+
+constexpr unsigned long long kLaneBit1 = 0xccccccccccccccccull, kLaneBit0 = 0xaaaaaaaaaaaaaaaaull;
+
+// Sums of a[0..7] and of c[0..N-1] over the eight lanes of equal y, into a[0] and c[0]: lane x of
+// the eight holds value sum_x_slot<8>(x) of a and sum_x_slot<N>(x) of c (none where that is -1).
+// Every lane must be active.
+template <int N>
+__device__ __forceinline__ int sum_x_slot(int x) {
+  const int b0 = x & 1, b1 = (x >> 1) & 1, b2 = x >> 2;
+  int v;
+  if (N > 6) v = 4 * b0 + 2 * b1 + b2;
+  else if (N > 4) v = b0 ? (b1 ? -1 : 4 + b2) : 2 * b1 + b2;
+  else v = b0 ? -1 : 2 * b1 + b2;
+  return v < N ? v : -1;
 }
 
-// The adds below are kept out of FMA contraction with any product that feeds them: an FMA
-// cannot take a DPP operand, a plain add folds the lane exchange into itself.
-template <int CTRL>
-__device__ __forceinline__ float pair_level(float x, float y, bool bit) {
+__device__ __forceinline__ void sum_x(float (&a)[8], float (&c)[6]) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %6, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %8, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %10, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %12, %12, %12 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %2, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %4, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %6, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %8, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %10, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %12, %13, %13 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %8, %8, %8 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %10, %10, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %12, %12, %12 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %2, %14\n\t"
+      "v_cndmask_b32_e64 %4, %4, %6, %14\n\t"
+      "v_cndmask_b32_e64 %8, %8, %10, %14\n\t"
+      "v_add_f32_dpp %12, %12, %12 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %8, %8, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %4, %15\n\t"
+      "v_cndmask_b32_e64 %8, %8, %12, %15"
+      : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]), "+&v"(a[7]),
+        "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5])
+      : "s"(kLaneBit1), "s"(kLaneBit0));
+}
+
+__device__ __forceinline__ void sum_x(float (&a)[8], float (&c)[7]) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %6, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %8, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %10, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %12, %12, %12 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %14, %14, %14 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %2, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %4, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %6, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %8, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %10, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %12, %13, %13 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %8, %8, %8 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %10, %10, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %12, %12, %12 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %14, %14, %14 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %2, %15\n\t"
+      "v_cndmask_b32_e64 %4, %4, %6, %15\n\t"
+      "v_cndmask_b32_e64 %8, %8, %10, %15\n\t"
+      "v_cndmask_b32_e64 %12, %12, %14, %15\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %8, %8, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %12, %12, %12 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %4, %16\n\t"
+      "v_cndmask_b32_e64 %8, %8, %12, %16"
+      : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]), "+&v"(a[7]),
+        "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]), "+&v"(c[6])
+      : "s"(kLaneBit1), "s"(kLaneBit0));
+}
+
+// The same for three values (into c[0]).
+__device__ __forceinline__ void sum_x(float (&c)[3]) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %2, %3\n\t"
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+      : "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2])
+      : "s"(kLaneBit1));
+}
+
+// Lane bit 3 (partner l ^ 8, a row rotation by 8) of three pairs: a <- (bit clear: a, set: b).
+// The trailing s_nop is for the permlane swaps that read the results.
+__device__ __forceinline__ void pair_bit3(float& a0, float b0, float& a1, float b1, float& a2, float b2) {
+  asm volatile("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "s_nop 1"
+      : "+&v"(a0), "+&v"(a1), "+&v"(a2)
+      : "v"(b0), "v"(b1), "v"(b2));
+}
+
+__device__ __forceinline__ void pair_bit3(float& a, float b) {
+  asm volatile("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "s_nop 1"
+      : "+&v"(a)
+      : "v"(b));
+}
+
+// Lane bits 5 and 4: lower half keeps a, upper half b (sum_bit5); even rows a, odd rows b.
+__device__ __forceinline__ float sum_bit5(float a, float b) {
 #pragma clang fp contract(off)
-  const float sx = x + TSR_DPP(x, CTRL, 0xF, 0xF);
-  const float sy = y + TSR_DPP(y, CTRL, 0xF, 0xF);
-  return bit ? sy : sx;
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
-__device__ __forceinline__ float wave_sum20(const float* v) {
+__device__ __forceinline__ float sum_bit4(float a, float b) {
 #pragma clang fp contract(off)
-  float s[10];
-#pragma unroll
-  for (int i = 0; i < 10; ++i) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]), false,
-                                                    false);
-    s[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  }
-  float t[5];
-#pragma unroll
-  for (int j = 0; j < 5; ++j) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[2 * j]), __float_as_uint(s[2 * j + 1]), false,
-                                                    false);
-    t[j] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  }
-  const int x = threadIdx.x & 15;
-  const bool b2 = x & 4, b3 = x & 8;
-  const float a0 = pair_level<0x128>(t[0], t[1], b3);                  // row_ror:8
-  const float a1 = pair_level<0x128>(t[2], t[3], b3);
-  float a2 = t[4] + TSR_DPP(t[4], 0x128, 0xF, 0xF);
-  float bb = pair_level<0x141>(a0, a1, b2);                            // row_half_mirror
-  a2 += TSR_DPP(a2, 0x141, 0xF, 0xF);
-  bb += TSR_DPP(bb, 0x4E, 0xF, 0xF);                                   // quad_perm [2,3,0,1]
-  a2 += TSR_DPP(a2, 0x4E, 0xF, 0xF);
-  bb += TSR_DPP(bb, 0xB1, 0xF, 0xF);                                   // quad_perm [1,0,3,2]
-  a2 += TSR_DPP(a2, 0xB1, 0xF, 0xF);
-  float out = (x & 3) == 0 ? bb : a2;
-  // keeps the sums in this (full-wave) part of the code instead of letting them move into a
-  // caller's branch on the slot
-  asm volatile("" : "+v"(out));
-  return out;
-}
-
-// The same butterfly over 24 values: the third permlane16 pair (values 16..23) is split by bit 3
-// like the first two and then summed over bits 2..0; its totals are read on lanes x = 1 (bit 3
-// clear) and x = 9 (bit 3 set) of each row.  Result: value wave_sum24_slot() on the 24 lanes
-// where that is not -1.  Every lane must be active.
-__device__ __forceinline__ int wave_sum24_slot() {
-  const int r = (threadIdx.x & 63) >> 4, x = threadIdx.x & 15;
-  const int rmap = r == 0 ? 0 : (r == 1 ? 2 : (r == 2 ? 1 : 3));
-  const int b3 = (x >> 3) & 1;
-  if ((x & 3) == 0) return 4 * (2 * ((x >> 2) & 1) + b3) + rmap;
-  return (x & 7) == 1 ? 16 + 4 * b3 + rmap : -1;
-}
-
-__device__ __forceinline__ float wave_sum24(const float* v) {
-#pragma clang fp contract(off)
-  float s[12];
-#pragma unroll
-  for (int i = 0; i < 12; ++i) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]), false,
-                                                    false);
-    s[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  }
-  float t[6];
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[2 * j]), __float_as_uint(s[2 * j + 1]), false,
-                                                    false);
-    t[j] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  }
-  const int x = threadIdx.x & 15;
-  const bool b2 = x & 4, b3 = x & 8;
-  const float a0 = pair_level<0x128>(t[0], t[1], b3);                  // row_ror:8
-  const float a1 = pair_level<0x128>(t[2], t[3], b3);
-  float a2 = pair_level<0x128>(t[4], t[5], b3);
-  float bb = pair_level<0x141>(a0, a1, b2);                            // row_half_mirror
-  a2 += TSR_DPP(a2, 0x141, 0xF, 0xF);
-  bb += TSR_DPP(bb, 0x4E, 0xF, 0xF);                                   // quad_perm [2,3,0,1]
-  a2 += TSR_DPP(a2, 0x4E, 0xF, 0xF);
-  bb += TSR_DPP(bb, 0xB1, 0xF, 0xF);                                   // quad_perm [1,0,3,2]
-  a2 += TSR_DPP(a2, 0xB1, 0xF, 0xF);
-  float out = (x & 3) == 0 ? bb : a2;
-  asm volatile("" : "+v"(out));
-  return out;
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
 __device__ __forceinline__ int wave_max_int(int v) {

@@ -1215,21 +1215,30 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
   }
 }
 
-// Float outputs of the FP64 pose and loss sums (adding their kSumCopies copies).
+// Float outputs of the FP64 pose and loss sums: one wave per sum adds its kSumCopies copies, one
+// per lane, so that the copies cost one memory round trip (a loop over them by one thread took
+// eight).
 __device__ __forceinline__ void write_sums(const ViewTable& vt, const double* __restrict__ pose_acc,
                                            float* __restrict__ grad_pose, const double* __restrict__ loss_acc,
                                            float* __restrict__ loss) {
-  const int nv = vt.n_views;
-  for (int k = threadIdx.x; k < 7 * nv; k += blockDim.x) {
-    const bool is_pose = k < 6 * nv;
-    if (is_pose ? !grad_pose : !loss) continue;
-    const double* src = is_pose ? pose_acc + k : loss_acc + (k - 6 * nv);
-    const int stride = is_pose ? 6 * nv : nv;
-    double t = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < kSumCopies; ++c) t += src[(int64_t)c * stride];
-    if (is_pose) grad_pose[k] = (float)t;
-    else loss[k - 6 * nv] = (float)t;
+  static_assert(kSumCopies == kWave, "one copy per lane");
+  const int nv = vt.n_views, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  constexpr int kU = 4;                      // sums per wave in flight
+  for (int k0 = threadIdx.x >> 6; k0 < 7 * nv; k0 += kU * nw) {
+    double t[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int k = k0 + u * nw;
+      const double* src = k < 6 * nv ? pose_acc + k : loss_acc + (k - 6 * nv);
+      t[u] = k < 7 * nv ? src[(int64_t)lane * (k < 6 * nv ? 6 * nv : nv)] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int k = k0 + u * nw;
+      for (int o = 32; o > 0; o >>= 1) t[u] += __shfl_xor(t[u], o, 64);
+      if (lane == 0 && k < 6 * nv && grad_pose) grad_pose[k] = (float)t[u];
+      if (lane == 0 && k >= 6 * nv && k < 7 * nv && loss) loss[k - 6 * nv] = (float)t[u];
+    }
   }
 }
 
@@ -1506,53 +1515,48 @@ __global__ void k_pose_compose(const float* __restrict__ tau, const float* __res
 // Gradient with respect to tau of a loss evaluated at Exp(tau) T, from its left-perturbation
 // gradient g at Exp(tau) T: Exp(tau + d) = Exp(J_l(tau) d) Exp(tau) to first order, so
 // dL/dtau = J_l(tau)^T g.  J_l(tau) = sum_n ad(tau)^n / (n+1)! with the se(3) adjoint
-// ad(rho, theta) = [[theta]x, [rho]x; 0, [theta]x] (translation first); the series is summed
-// in FP64 until its terms fall below 1e-17 of the running sum (at most 80 terms).
+// ad(rho, theta) = [[theta]x, [rho]x; 0, [theta]x] (translation first), so J_l^T g is summed by
+// its terms t_0 = g, t_n = ad^T t_(n-1) / (n+1): with t = (a, b), ad^T t = (a x theta, a x rho +
+// b x theta), four cross products' worth of FP64 per term instead of the 6x6 powers (45 us for
+// one view, 5 with the vectors: one lane runs it, so its length is its instructions).  Summed
+// until, past the largest terms (n + 1 > 2 |ad|), a term falls below 1e-17 of the running sum, at
+// most 80 terms.
 __global__ void k_pose_tau_grad(const float* __restrict__ tau, const float* __restrict__ grad_pose, int n_views,
                                 float* __restrict__ grad_tau) {
   const int v = threadIdx.x;
   if (v >= n_views) return;
-  double ad[6][6];
-  for (int i = 0; i < 6; ++i)
-    for (int j = 0; j < 6; ++j) ad[i][j] = 0.0;
-  const double r0 = tau[6 * v], r1 = tau[6 * v + 1], r2 = tau[6 * v + 2];
-  const double t0 = tau[6 * v + 3], t1 = tau[6 * v + 4], t2 = tau[6 * v + 5];
-  for (int b = 0; b < 2; ++b) {          // [theta]x on the two diagonal blocks
-    const int o = 3 * b;
-    ad[o][o + 1] = -t2; ad[o][o + 2] = t1;
-    ad[o + 1][o] = t2;  ad[o + 1][o + 2] = -t0;
-    ad[o + 2][o] = -t1; ad[o + 2][o + 1] = t0;
+  double x[6], a[3], b[3], sum[6];
+  for (int i = 0; i < 6; ++i) x[i] = (double)tau[6 * v + i];
+  for (int i = 0; i < 3; ++i) {                      // (grad_tau may alias grad_pose)
+    sum[i] = a[i] = (double)grad_pose[6 * v + i];
+    sum[3 + i] = b[i] = (double)grad_pose[6 * v + 3 + i];
   }
-  ad[0][4] = -r2; ad[0][5] = r1;          // [rho]x in the upper right block
-  ad[1][3] = r2;  ad[1][5] = -r0;
-  ad[2][3] = -r1; ad[2][4] = r0;
-  double term[6][6], J[6][6], nxt[6][6];
-  for (int i = 0; i < 6; ++i)
-    for (int j = 0; j < 6; ++j) term[i][j] = J[i][j] = (i == j) ? 1.0 : 0.0;
-  for (int n = 1; n <= 80; ++n) {        // term = ad^n / (n+1)!
-    double tmax = 0.0, jmax = 0.0;
-    for (int i = 0; i < 6; ++i)
-      for (int j = 0; j < 6; ++j) {
-        double s = 0.0;
-        for (int k = 0; k < 6; ++k) s += term[i][k] * ad[k][j];
-        nxt[i][j] = s / (double)(n + 1);
-      }
-    for (int i = 0; i < 6; ++i)
-      for (int j = 0; j < 6; ++j) {
-        term[i][j] = nxt[i][j];
-        J[i][j] += term[i][j];
-        tmax = fmax(tmax, fabs(term[i][j]));
-        jmax = fmax(jmax, fabs(J[i][j]));
-      }
-    if (tmax <= 1e-17 * jmax) break;
+  const double* rho = x;
+  const double* th = x + 3;
+  double bound = 0.0;                                // >= the row sums of |ad^T|
+  for (int i = 0; i < 6; ++i) bound += fabs(x[i]);
+  for (int n = 1; n <= 80; ++n) {
+    const double inv = 1.0 / (double)(n + 1);
+    double na[3], nb[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int j = (i + 1) % 3, k = (i + 2) % 3;
+      na[i] = (a[j] * th[k] - a[k] * th[j]) * inv;
+      nb[i] = ((a[j] * rho[k] - a[k] * rho[j]) + (b[j] * th[k] - b[k] * th[j])) * inv;
+    }
+    double tmax = 0.0, smax = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      a[i] = na[i];
+      b[i] = nb[i];
+      sum[i] += a[i];
+      sum[3 + i] += b[i];
+      tmax = fmax(tmax, fmax(fabs(a[i]), fabs(b[i])));
+      smax = fmax(smax, fmax(fabs(sum[i]), fabs(sum[3 + i])));
+    }
+    if ((double)(n + 1) > 2.0 * bound && tmax <= 1e-17 * smax) break;
   }
-  double g[6];
-  for (int i = 0; i < 6; ++i) g[i] = (double)grad_pose[6 * v + i];   // (grad_tau may alias grad_pose)
-  for (int j = 0; j < 6; ++j) {
-    double s = 0.0;
-    for (int i = 0; i < 6; ++i) s += J[i][j] * g[i];
-    grad_tau[6 * v + j] = (float)s;
-  }
+  for (int j = 0; j < 6; ++j) grad_tau[6 * v + j] = (float)sum[j];
 }
 
 // ---------------------------------------------------------------------------- launchers

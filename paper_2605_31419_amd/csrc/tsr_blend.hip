@@ -8,13 +8,18 @@
 // loads that go straight to LDS, and read by all lanes as broadcasts.
 //
 // What bounds the walks (1200x680 view of 1M faces, fused kernel): a wave alone on its SIMD issues
-// one instruction in about five cycles, so the longest tile's four waves take about 0.37 us per
-// listed face whatever else runs (514 faces: 211 us of a 212 us launch before the walks took two
-// faces per round, 160 of 171 now), and below that the number of VALU instructions per visit.
-// Two faces per round, records loaded a face ahead, the paired gradient sums of tsr_device.h
-// and the staging without registers (72 -> 84 VGPRs instead of 120) took the step from 278 to
-// 244 us, the 8-view window of 500k faces from 700 to 641 us, the photometric step from 368 to
-// 335 us and the face statistics from 139 to 125 us.
+// one instruction in about five cycles, so the longest tile's four waves take about 0.34 us per
+// listed face whatever else runs (594 faces: 151 us of a 156 us launch), and below that the number of
+// VALU instructions per visit.  The forward takes two faces per round, its records loaded a face
+// ahead and staged without registers (72 -> 84 VGPRs instead of 120); the backward evaluates the two
+// faces of a round in the two halves of the wave, two pixels a lane, so that one set of gradient sums
+// serves both.  Per listed face of the longest tile: forward 140 -> 115 ns, backward 315 -> 258 with
+// two faces one after the other and 226 in the two halves; the step 278 -> 244 -> 238 us, the 8-view
+// window of 500k faces 700 -> 641 -> 629 us, the photometric step 368 -> 335 -> 328 us, the 8-view
+// mapping step 2.28 -> 2.13 -> 2.09 ms and the face statistics (no backward) 139 -> 125 us.
+// (Both halves in the forward too, with eight waves of 8x4 pixels per tile, cut the longest tile's
+// walk to 97 + 157 ns per face, but twice the waves with their set-up and hit masks, and 1.4 times
+// the gradient atomics, made every case slower: mapping 2.53 ms.)
 #include "tsr_internal.h"
 
 namespace tsr {
@@ -339,6 +344,16 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
   return ballot(hit);
 }
 
+// Swaps the upper half of a with the lower half of b.
+struct Halves {
+  float f0, f1;
+};
+
+__device__ __forceinline__ Halves swap_halves(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+
 struct FwdState {
   float T, C0, C1, C2, D, Tb;
   float N0, N1, N2;        // composited world normal (normal channels)
@@ -465,44 +480,29 @@ struct FaceTerms {
   float p0[8], p1[p1_terms<SM>()], p2[3];
 };
 
-// Sums of two faces' terms over the wave; lane l holds one total (which one: grad_lane).
-//   sum over x: P0, P1 (P2) of each face (sum_face_x); Q0 = P0 dy of the lane's row of pixels;
-//   bit 3: U = (P0, P1) of each face, V = (Q0 of face 0, Q0 of face 1), R = (P2, P2);
-//   bit 5: X = (U of face 0, U of face 1), Y = V (with the normals: (V, R)); bit 4: (X, Y).
-struct FaceSums {
-  float p0, p1, p2, q0;
-};
-
+// Sums of the two faces' terms, each over its half of the wave; lane l holds one total of its
+// half's face (which one: grad_lane).  p0 and p1 over the row of pixels first, then Q0 = P0 dy, then
+// P0, P1, Q0 (and p2) over the rows.
 template <int SM>
-__device__ __forceinline__ FaceSums sum_face_x(FaceTerms<SM>& ft, float dy) {
+__device__ __forceinline__ float sum_face(FaceTerms<SM>& ft, float dy) {
   sum_x(ft.p0, ft.p1);
-  if constexpr (normal_mode<SM>()) sum_x(ft.p2);
-  return FaceSums{ft.p0[0], ft.p1[0], normal_mode<SM>() ? ft.p2[0] : 0.f, ft.p0[0] * dy};
-}
-
-template <int SM>
-__device__ __forceinline__ float sum_faces(FaceSums& f0, FaceSums& f1) {
-  pair_bit3(f0.p0, f0.p1, f1.p0, f1.p1, f0.q0, f1.q0);
-  const float x = sum_bit5(f0.p0, f1.p0);
-  float y;
+  float q0 = ft.p0[0] * dy, q1 = ft.p0[4] * dy, out;
   if constexpr (normal_mode<SM>()) {
-    pair_bit3(f0.p2, f1.p2);
-    y = sum_bit5(f0.q0, f0.p2);
+    sum_x(ft.p2);
+    out = sum_y(ft.p0[0], ft.p0[4], ft.p1[0], ft.p1[4], q0, q1, ft.p2[0]);
   } else {
-    y = sum_bit5(f0.q0, f0.q0);
+    out = sum_y(ft.p0[0], ft.p0[4], ft.p1[0], ft.p1[4], q0, q1);
   }
-  float out = sum_bit4(x, y);
   // keeps the sums in this (full-wave) part of the code instead of letting them move into a
   // caller's branch on the lane
   asm volatile("" : "+v"(out));
   return out;
 }
 
-// Where this lane's total of sum_faces goes: which face of the pair (-1: the lane holds none),
-// and the address base + id * stride of its accumulator (acc: the gradient accumulator, whose
-// element type may be double).
+// Where this lane's total of sum_face goes: whether it holds one, and the address base + id *
+// stride of its accumulator (acc: the gradient accumulator, whose element type may be double).
 struct GradLane {
-  int face;
+  bool any;
   uint32_t stride;
   char* base;
   bool acc;
@@ -511,39 +511,32 @@ struct GradLane {
 template <int SM>
 __device__ __forceinline__ GradLane grad_lane(acc_t* grad_acc, float* sig_acc, float* persp_acc, float* gacc,
                                               int64_t moff) {
-  const int lane = threadIdx.x & 63, x = lane & 7;
-  const bool b3 = lane & 8, b4 = lane & 16, b5 = lane & 32;
-  int face = -1, k = -1, where = 0;      // where: 0 gradient accumulator, 1 exponent, 2 W plane, 3 normal
-  if (!b4) {
-    face = b5 ? 1 : 0;
-    if (!b3) {
-      const int i = sum_x_slot<8>(x);
-      k = i < 3 ? kGEdge + 3 * i + 2 : (i < 6 ? kGCol + 3 * (i - 3) + 2 : (i == 6 ? (int)kGOpa : (int)kGZ));
-    } else {
-      const int i = sum_x_slot<p1_terms<SM>()>(x);
-      if (i == 6) {
-        where = persp_mode<SM>() ? 2 : 1;
-        k = 0;
-      } else if (i >= 0) {
-        k = i < 3 ? kGEdge + 3 * i : kGCol + 3 * (i - 3);
-      }
+  const int lane = threadIdx.x & 63;
+  const int b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1;
+  int k = -1, where = 0;      // where: 0 gradient accumulator, 1 exponent, 2 W plane, 3 normal
+  const int i = 4 * b1 + 2 * b2 + b3;                // the lane's value of p0
+  if (!b4 && !b0) {
+    k = i < 3 ? kGEdge + 3 * i + 2 : (i < 6 ? kGCol + 3 * (i - 3) + 2 : (i == 6 ? (int)kGOpa : (int)kGZ));
+  } else if (!b4) {
+    if (i < 6) {
+      k = i < 3 ? kGEdge + 3 * i : kGCol + 3 * (i - 3);
+    } else if (i == 6 && p1_terms<SM>() == 7) {
+      where = persp_mode<SM>() ? 2 : 1;
+      k = 0;
     }
-  } else if (!b5) {
-    face = b3 ? 1 : 0;
-    const int i = sum_x_slot<8>(x);
+  } else if (!b0) {
     if (i < 6) {
       k = i < 3 ? kGEdge + 3 * i + 1 : kGCol + 3 * (i - 3) + 1;
     } else if (persp_mode<SM>() && i == 7) {
       where = 2;
       k = 1;
     }
-  } else if (normal_mode<SM>()) {
-    face = b3 ? 1 : 0;
+  } else if (normal_mode<SM>() && i < 3) {
     where = 3;
-    k = sum_x_slot<3>(x);
+    k = i;
   }
   GradLane g;
-  g.face = k >= 0 ? face : -1;
+  g.any = k >= 0;
   g.acc = where == 0;
   const int kk = k >= 0 ? k : 0;
   if (where == 0) {
@@ -574,7 +567,9 @@ __device__ __forceinline__ void add_total(const GradLane& gl, uint32_t g, float 
 }
 
 // Back-to-front walk (Sec. 3.3).  T before each face is recovered by division from the
-// transmittance before the last blended face.  What lies behind the current face, composited
+// transmittance before the last blended face.  The faces of a batch's mask are taken two per round,
+// one in each half of the wave (a lane: one face, two pixels), so one butterfly sums both faces'
+// terms and a pixel's two terms are added before it.  What lies behind the current face, composited
 // from transmittance 1 (colour B, depth BD, opacity BA), enters dL/dalpha only through
 // S = gC.B + gD BD - gT BA, so S is carried instead: with P = gC.c + gD z - gT for the face,
 // dL/dalpha = T (P - S) and S <- alpha P + (1 - alpha) S.  Per-face sums of the 20
@@ -603,9 +598,32 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
   const GradLane gl = grad_lane<SM>(grad_acc, sig_acc, persp_acc,
                                     normal_mode<SM>() ? reinterpret_cast<float*>(nin->gacc) : nullptr,
                                     normal_mode<SM>() ? (int64_t)c.view * nin->M : 0);
-  float Tcur = Tb;
+  // From one pixel per lane to the walk's layout: the lower half of the wave takes the first face of
+  // a pair, the upper half the second, each lane two pixels of it, A and B four apart in x.
+  // Lane bits 2 and 3 are x, bits 0, 1 and 4 y.  What is carried from face to face (T, S) is held
+  // once per pixel: of A in the lower half and of B in the upper one.
+  const bool upper = lane >= 32;
+  const int xl = (lane >> 2) & 3, yl = (lane & 3) | ((lane >> 2) & 4);
+  const int la = 8 * yl + xl, lb = la + 4;           // lanes of the pixels before
+  int lastp[2];
+  PixGrad pp[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int l = q ? lb : la;
+    lastp[q] = __shfl(last, l, 64);
+    pp[q] = PixGrad{__shfl(pg.g0, l, 64), __shfl(pg.g1, l, 64), __shfl(pg.g2, l, 64), __shfl(pg.gd, l, 64),
+                    __shfl(pg.gt, l, 64)};
+    if constexpr (normal_mode<SM>()) {
+      pp[q].gn0 = __shfl(pg.gn0, l, 64);
+      pp[q].gn1 = __shfl(pg.gn1, l, 64);
+      pp[q].gn2 = __shfl(pg.gn2, l, 64);
+    }
+  }
+  const float Tl = __shfl(Tb, upper ? lb : la, 64);  // T before the last blended face
+  const int lastl = upper ? lastp[1] : lastp[0];
+  float Tcur = Tl;
   float S = 0.f;
-  const float dxb = (float)c.px, dyb = (float)c.py;
+  const float dxb = (float)(c.bx + xl), dyb = (float)(c.by + yl);
   for (int s1 = top + 1, s0; s1 > (int)c.start; s1 = s0) {
     // cooperative spans start where the forward's do, so that the last one it staged is still there
     s0 = COOP ? (int)c.start + (s1 - 1 - (int)c.start) / kStage * kStage : max((int)c.start, s1 - kStage);
@@ -624,94 +642,112 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
     unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by);
     if (wlast - b0 < 63) mask &= (2ull << (wlast - b0)) - 1ull;     // faces after the wave's last
     if (mask == 0ull) continue;
-    auto visit = [&](const Rec& rc, int j) -> FaceSums {
-      // Every lane evaluates the face; lanes that do not blend it (not covered, or behind their
-      // last face) get alpha 0 and zero gradient scales, so all sums need no branches.
-      const int idx = b0 + j;
-      const float dx = dxb - rc.f[kRecU0];
+    int j0 = last_bit(mask), j1 = last_bit(mask);
+    int jl = upper ? j1 : j0;           // this lane's face
+    Rec rc;
+    load_rec(sr, jl, rc);
+    for (;;) {
+      // Every lane evaluates its face; pixels that do not blend it (not covered, or behind their
+      // last face) get alpha 0 and zero gradient scales, so all sums need no branches.  The empty
+      // record takes no list position (b0 + 64 may be that of a later face).
+      const int i0 = b0 + j0, i1 = j1 == kBatch ? 0x7fffffff : b0 + j1, il = b0 + jl;
+      // the id that this lane's total goes to (its load is as old as the sums when it is used)
+      const uint32_t id = sf[jl];
+      const float dx = dxb - rc.f[kRecU0], dxB = dx + 4.f;
       const float dy = dyb - rc.f[kRecV0];
-      PixelEval e;
-      const bool act = eval_face<SM>(rc, dx, dy, sigma, e) && (idx <= last);
-      FaceTerms<SM> ft;
-      const float alpha = act ? e.alpha : 0.f;
-      const float om = 1.f - alpha;
-      // T before this face: the stored value at the last face, else T_after / (1 - alpha), which
-      // is T_after itself where the face is not blended (rcp(1) = 1; the empty record's idx may be
-      // that of a later face)
-      const float Tj = (act && idx == last) ? Tb : Tcur * __builtin_amdgcn_rcpf(om);
-      Tcur = Tj;
-      const float zf = e.zp;
-      const float c0 = e.c0, c1 = e.c1, c2 = e.c2;
-      const float w = alpha * Tj;
-      // colour plane gradients: dL/dc_ch(p) = gC_ch alpha T, and c_ch = P dx + Q dy + R
-      float gc0 = pg.g0 * w, gc1 = pg.g1 * w, gc2 = pg.g2 * w;
-      float gz = 0.f;
-      if constexpr (persp_mode<SM>()) {
-        // c_ch = N_ch / W, depth = 1 / W: dL/dN_ch = gC_ch w / W, dL/dW = -(gC.c + gD depth) w / W
-        gz = -(fmaf(pg.g0, c0, fmaf(pg.g1, c1, fmaf(pg.g2, c2, pg.gd * zf)))) * w * zf;
-        gc0 *= zf;
-        gc1 *= zf;
-        gc2 *= zf;
-      } else {
-        gz = pg.gd * w;
+      PixelEval e[2];
+      bool act[2];
+      float alpha[2], P[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        act[q] = eval_face<SM>(rc, q ? dxB : dx, dy, sigma, e[q]) && (il <= lastp[q]);
+        alpha[q] = act[q] ? e[q].alpha : 0.f;
+        // dL/dalpha = T (gC.(c - B) + gD (z - BD) - gT (1 - BA)) = T (P - S)
+        const PixGrad& g = pp[q];
+        P[q] = fmaf(g.g0, e[q].c0, fmaf(g.g1, e[q].c1, fmaf(g.g2, e[q].c2, fmaf(g.gd, e[q].zp, -g.gt))));
       }
-      // dL/dalpha = T (gC.(c - B) + gD (z - BD) - gT (1 - BA)) = T (P - S)
-      float P = fmaf(pg.g0, c0, fmaf(pg.g1, c1, fmaf(pg.g2, c2, fmaf(pg.gd, zf, -pg.gt))));
       if constexpr (normal_mode<SM>()) {
         // the face's normal is a colour constant over the face: it enters dL/dalpha like one
-        const float4 nf = sn[j];
-        P = fmaf(pg.gn0, nf.x, fmaf(pg.gn1, nf.y, fmaf(pg.gn2, nf.z, P)));
-      }
-      const float galpha = act ? Tj * (P - S) : 0.f;
-      S = fmaf(alpha, P, om * S);
-      const float gI = galpha * rc.f[kRecOpa];
-      float grho = 0.f;
-      if constexpr (exp_mode<SM>() == 1) grho = e.rho < 1.f ? gI : 0.f;
-      else grho = (act && e.rho < 1.f) ? gI * face_sigma<SM>(rc.f, sigma) * e.I * __builtin_amdgcn_rcpf(e.rho) : 0.f;   // sigma I / rho
-      // only the edge attaining the minimum receives the window gradient (the others' differences
-      // are exact zeros)
-      const float gk0 = e.k0 ? grho : 0.f, g12 = grho - gk0;
-      const float gk1 = e.k1 ? g12 : 0.f, gk2 = g12 - gk1;
-      float* p0 = ft.p0;
-      p0[0] = gk0; p0[1] = gk1; p0[2] = gk2;
-      p0[3] = gc0; p0[4] = gc1; p0[5] = gc2;
-      p0[6] = galpha * e.I;
-      p0[7] = gz;
-      float* p1 = ft.p1;
+        const float4 nf = sn[jl];
 #pragma unroll
-      for (int k = 0; k < 6; ++k) p1[k] = p0[k] * dx;
-      if constexpr (persp_mode<SM>()) p1[6] = gz * dx;
-      // the face's own exponent: dI/dsigma = I ln(rho) for 0 < rho < 1 (act implies rho > 0)
-      if constexpr (exp_mode<SM>() == 4)
-        p1[6] = (act && e.rho < 1.f) ? gI * e.I * (0.69314718055994531f * log2f(e.rho)) : 0.f;
-      if constexpr (normal_mode<SM>()) {
-        // dE/dn_F = sum over the face's pixels of gN alpha T
-        ft.p2[0] = pg.gn0 * w;
-        ft.p2[1] = pg.gn1 * w;
-        ft.p2[2] = pg.gn2 * w;
+        for (int q = 0; q < 2; ++q) P[q] = fmaf(pp[q].gn0, nf.x, fmaf(pp[q].gn1, nf.y, fmaf(pp[q].gn2, nf.z, P[q])));
       }
-      return sum_face_x<SM>(ft, dy);
-    };
-    int j0 = last_bit(mask), j1 = last_bit(mask);
-    Rec r0, r1;
-    load_rec(sr, j0, r0);
-    load_rec(sr, j1, r1);
-    for (;;) {
-      // the id that this lane's total goes to (its load is as old as the sums when it is used)
-      const uint32_t id = sf[gl.face > 0 ? j1 : j0];
-      FaceSums f0 = visit(r0, j0);
+      const float opa = rc.f[kRecOpa], sig = face_sigma<SM>(rc.f, sigma);
       j0 = last_bit(mask);
-      __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
-      load_rec(sr, j0, r0);
-      __builtin_amdgcn_sched_barrier(0);
-      FaceSums f1 = visit(r1, j1);
       j1 = last_bit(mask);
+      jl = upper ? j1 : j0;
+      __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
+      load_rec(sr, jl, rc);
       __builtin_amdgcn_sched_barrier(0);
-      load_rec(sr, j1, r1);
-      __builtin_amdgcn_sched_barrier(0);
-      const float tot = sum_faces<SM>(f0, f1);
+      // one pixel per lane, both faces: T before each face is the stored value at the last face,
+      // else T_after / (1 - alpha), which is T_after itself where the face is not blended (rcp(1) = 1)
+      const Halves ca = swap_halves(alpha[0], alpha[1]), cp = swap_halves(P[0], P[1]);
+      const float om0 = 1.f - ca.f0, om1 = 1.f - ca.f1;
+      const float T0 = i0 == lastl ? Tl : Tcur * __builtin_amdgcn_rcpf(om0);
+      const float T1 = i1 == lastl ? Tl : T0 * __builtin_amdgcn_rcpf(om1);
+      const float S1 = fmaf(ca.f0, cp.f0, om0 * S);
+      // and back: one face per lane, both pixels
+      const Halves Tq = swap_halves(T0, T1), Sq = swap_halves(S, S1);
+      Tcur = T1;
+      S = fmaf(ca.f1, cp.f1, om1 * S1);
+      // Sums of the two pixels' terms and of their moments with respect to dx.
+      // colour plane gradients: dL/dc_ch(p) = gC_ch alpha T, and c_ch = P dx + Q dy + R
+      FaceTerms<SM> ft;
+      auto add = [&](int k, float ta, float tb) {
+        ft.p0[k] = ta + tb;
+        if (k < 6) ft.p1[k] = fmaf(tb, dxB, ta * dx);
+      };
+      float galpha[2], gc[2][3], gz[2], gk[2][3];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const PixGrad& g = pp[q];
+        const float Tj = q ? Tq.f1 : Tq.f0;
+        galpha[q] = act[q] ? Tj * (P[q] - (q ? Sq.f1 : Sq.f0)) : 0.f;
+        const float w = alpha[q] * Tj;
+        gc[q][0] = g.g0 * w;
+        gc[q][1] = g.g1 * w;
+        gc[q][2] = g.g2 * w;
+        if constexpr (persp_mode<SM>()) {
+          // c_ch = N_ch / W, depth = 1 / W: dL/dN_ch = gC_ch w / W, dL/dW = -(gC.c + gD depth) w / W
+          const float zf = e[q].zp;
+          gz[q] = -(fmaf(g.g0, e[q].c0, fmaf(g.g1, e[q].c1, fmaf(g.g2, e[q].c2, g.gd * zf)))) * w * zf;
+#pragma unroll
+          for (int ch = 0; ch < 3; ++ch) gc[q][ch] *= zf;
+        } else {
+          gz[q] = g.gd * w;
+        }
+        if constexpr (normal_mode<SM>()) {
+          // dE/dn_F = sum over the face's pixels of gN alpha T
+          ft.p2[0] = q ? fmaf(g.gn0, w, ft.p2[0]) : g.gn0 * w;
+          ft.p2[1] = q ? fmaf(g.gn1, w, ft.p2[1]) : g.gn1 * w;
+          ft.p2[2] = q ? fmaf(g.gn2, w, ft.p2[2]) : g.gn2 * w;
+        }
+        const float gI = galpha[q] * opa, rho = e[q].rho;
+        float grho = 0.f;
+        if constexpr (exp_mode<SM>() == 1) grho = rho < 1.f ? gI : 0.f;
+        else grho = (act[q] && rho < 1.f) ? gI * sig * e[q].I * __builtin_amdgcn_rcpf(rho) : 0.f;   // sigma I / rho
+        // only the edge attaining the minimum receives the window gradient (the others' differences
+        // are exact zeros)
+        gk[q][0] = e[q].k0 ? grho : 0.f;
+        const float g12 = grho - gk[q][0];
+        gk[q][1] = e[q].k1 ? g12 : 0.f;
+        gk[q][2] = g12 - gk[q][1];
+        // the face's own exponent: dI/dsigma = I ln(rho) for 0 < rho < 1 (act implies rho > 0)
+        if constexpr (exp_mode<SM>() == 4) {
+          const float gs = (act[q] && rho < 1.f) ? gI * e[q].I * (0.69314718055994531f * log2f(rho)) : 0.f;
+          ft.p1[6] = q ? ft.p1[6] + gs : gs;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) add(k, gk[0][k], gk[1][k]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) add(3 + k, gc[0][k], gc[1][k]);
+      ft.p0[6] = fmaf(galpha[0], e[0].I, galpha[1] * e[1].I);
+      add(7, gz[0], gz[1]);
+      if constexpr (persp_mode<SM>()) ft.p1[6] = fmaf(gz[1], dxB, gz[0] * dx);
+      const float tot = sum_face<SM>(ft, dy);
       // one atomic per lane that holds a total (0 for the empty record)
-      if (gl.face >= 0) add_total<SM>(gl, id, tot);
+      if (gl.any) add_total<SM>(gl, id, tot);
       if (j0 == kBatch) break;
     }
     }
@@ -863,7 +899,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const flo
 // walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant).
 // Five workgroups per CU (96 registers a lane): the records of two faces in flight.
 template <int SM>
-__global__ __launch_bounds__(kBlock, 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
+__global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
                                                         const uint64_t* __restrict__ pairs,
                                                         const uint32_t* __restrict__ ranges, float sigma, float t_min,
                                                         float w_color, float w_depth,

@@ -103,169 +103,156 @@ __device__ __forceinline__ float wave_sum(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to_lane63(v)), 63));
 }
 
-// Sums of per-pixel gradient terms over the 8x8 pixels of a wave (lane = 8 y + x), for two faces
-// at a time.  The sums are taken in the order x, then y, so that a term's moment with respect to
-// y is formed after its sum over x (one product per eight pixels); every level is a transposing
-// butterfly: a pair of vectors (a, b) becomes one, the lanes on one side of the level's partner
-// bit keeping a summed with their partner and the others keeping b.
+// Sums of per-pixel gradient terms over the pixels of a wave's 8x8 quadrant, for two faces at a time,
+// one per half of the wave: a lane's terms are already the sums of two pixels of a row, lane bits 2
+// and 3 are x and bits 0, 1 and 4 y.  The sums are taken in the order x, then y, so that a term's
+// moment with respect to y is formed after its sum over x (one product per row of pixels); every
+// level is a transposing butterfly: a pair of vectors (a, b) becomes one, the lanes on one side of
+// the level's partner bit keeping a summed with their partner and the others keeping b.
 //
 // On gfx950 a wave64 v_permlane*_swap takes 8 cycles of a SIMD, a DPP add 4, a plain add or
-// multiply 2 (4 when nothing of the other kind can issue beside it).  Lane bits 2 and 3 are
-// therefore reduced by pairs of DPP adds that write only the banks of their side (a bank is four
-// lanes; no select needed), bits 1 and 0 by quad permutes and a select, and only the last two
-// levels, on the three or four vectors that are left of two faces, use swaps.
+// multiply 2 (4 when nothing of the other kind can issue beside it).  The x levels are pairs of DPP
+// row rotations that write only the banks of their side (a bank is four lanes; no select needed),
+// lane bits 1 and 0 quad permutes and a select, and only the last level, on the two vectors that are
+// left, a swap.  A lane that holds two pixels halves the sums' share of the work.
 //
-// The x levels are one asm block per face: the compiler cannot fold a masked DPP move into an add,
-// and inside a block the two wait states between a write and a DPP read of the same register are
-// kept by the order of the instructions (the hazard tables do not look inside asm: the leading
-// s_nop covers what was written just before).
+// The levels are asm blocks: the compiler cannot fold a masked DPP move into an add, and inside a
+// block the two wait states between a write and a DPP read of the same register are kept by the
+// order of the instructions (the hazard tables do not look inside asm: the leading s_nop covers
+// what was written just before).
 
 constexpr unsigned long long kLaneBit1 = 0xccccccccccccccccull, kLaneBit0 = 0xaaaaaaaaaaaaaaaaull;
 
-// Sums of a[0..7] and of c[0..N-1] over the eight lanes of equal y, into a[0] and c[0]: lane x of
-// the eight holds value sum_x_slot<8>(x) of a and sum_x_slot<N>(x) of c (none where that is -1).
+// Sums over x.  With b2, b3 the lane's bits: a[0] holds value 2 b2 + b3 of a, a[4] value 4 + 2 b2 +
+// b3; c[0] value 2 b2 + b3 of c, c[4] value 4 + b3 where b2 is 0, else value 6 if there are seven.
 // Every lane must be active.
-template <int N>
-__device__ __forceinline__ int sum_x_slot(int x) {
-  const int b0 = x & 1, b1 = (x >> 1) & 1, b2 = x >> 2;
-  int v;
-  if (N > 6) v = 4 * b0 + 2 * b1 + b2;
-  else if (N > 4) v = b0 ? (b1 ? -1 : 4 + b2) : 2 * b1 + b2;
-  else v = b0 ? -1 : 2 * b1 + b2;
-  return v < N ? v : -1;
-}
-
 __device__ __forceinline__ void sum_x(float (&a)[8], float (&c)[6]) {
   asm volatile(
       "s_nop 1\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %6, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %8, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %10, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %12, %12, %12 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %2, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %4, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %6, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %8, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %10, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %12, %13, %13 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %8, %8, %8 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %10, %10, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %12, %12, %12 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_e64 %0, %0, %2, %14\n\t"
-      "v_cndmask_b32_e64 %4, %4, %6, %14\n\t"
-      "v_cndmask_b32_e64 %8, %8, %10, %14\n\t"
-      "v_add_f32_dpp %12, %12, %12 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %8, %8, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_e64 %0, %0, %4, %15\n\t"
-      "v_cndmask_b32_e64 %8, %8, %12, %15"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %6, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %8, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %10, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %12, %12, %12 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %4, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %6, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %8, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %10, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %12, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %8, %8, %8 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %12, %12, %12 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %4, %6, %6 row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %8, %10, %10 row_ror:4 row_mask:0xf bank_mask:0xa"
       : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]), "+&v"(a[7]),
-        "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5])
-      : "s"(kLaneBit1), "s"(kLaneBit0));
+        "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]));
 }
 
 __device__ __forceinline__ void sum_x(float (&a)[8], float (&c)[7]) {
   asm volatile(
       "s_nop 1\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %6, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %8, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %10, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %12, %12, %12 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %14, %14, %14 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %2, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %4, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %6, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %8, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %10, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %12, %13, %13 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %8, %8, %8 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %10, %10, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %12, %12, %12 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %14, %14, %14 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_e64 %0, %0, %2, %15\n\t"
-      "v_cndmask_b32_e64 %4, %4, %6, %15\n\t"
-      "v_cndmask_b32_e64 %8, %8, %10, %15\n\t"
-      "v_cndmask_b32_e64 %12, %12, %14, %15\n\t"
-      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %8, %8, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %12, %12, %12 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_e64 %0, %0, %4, %16\n\t"
-      "v_cndmask_b32_e64 %8, %8, %12, %16"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %6, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %8, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %10, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %12, %12, %12 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %14, %14, %14 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %4, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %6, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %8, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %10, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %12, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %8, %8, %8 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %12, %12, %12 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %4, %6, %6 row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %8, %10, %10 row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %12, %14, %14 row_ror:4 row_mask:0xf bank_mask:0xa"
       : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]), "+&v"(a[7]),
-        "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]), "+&v"(c[6])
-      : "s"(kLaneBit1), "s"(kLaneBit0));
+        "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]), "+&v"(c[6]));
 }
 
-// The same for three values (into c[0]).
+// The same for three values: c[0] holds value b3 where b2 is 0, else value 2.
 __device__ __forceinline__ void sum_x(float (&c)[3]) {
   asm volatile(
       "s_nop 1\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "s_nop 0\n\t"
-      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_e64 %0, %0, %2, %3\n\t"
-      "s_nop 1\n\t"
-      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-      : "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2])
-      : "s"(kLaneBit1));
-}
-
-// Lane bit 3 (partner l ^ 8, a row rotation by 8) of three pairs: a <- (bit clear: a, set: b).
-// The trailing s_nop is for the permlane swaps that read the results.
-__device__ __forceinline__ void pair_bit3(float& a0, float b0, float& a1, float b1, float& a2, float b2) {
-  asm volatile("s_nop 1\n\t"
       "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %1, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %2, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "s_nop 1"
-      : "+&v"(a0), "+&v"(a1), "+&v"(a2)
-      : "v"(b0), "v"(b1), "v"(b2));
-}
-
-__device__ __forceinline__ void pair_bit3(float& a, float b) {
-  asm volatile("s_nop 1\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "s_nop 1"
-      : "+&v"(a)
-      : "v"(b));
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_ror:4 row_mask:0xf bank_mask:0xa"
+      : "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]));
 }
 
-// Lane bits 5 and 4: lower half keeps a, upper half b (sum_bit5); even rows a, odd rows b.
-__device__ __forceinline__ float sum_bit5(float a, float b) {
-#pragma clang fp contract(off)
-  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-
+// Lane bit 4: even rows of 16 lanes keep a, odd rows b.
 __device__ __forceinline__ float sum_bit4(float a, float b) {
 #pragma clang fp contract(off)
   const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+// Sums over y of (a0, a1), (c0, c1) and (q0, q1), each pair's second taken where lane bit 1 is set;
+// then the a's where lane bits 4 and 0 are 0, the c's where bit 0 is set, the q's where bit 4 is, and
+// the n's (if given) where both are.  The trailing s_nop is for the swap that reads the results.
+__device__ __forceinline__ float sum_y(float a0, float a1, float c0, float c1, float q0, float q1) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %1, %6\n\t"
+      "v_cndmask_b32_e64 %2, %2, %3, %6\n\t"
+      "v_cndmask_b32_e64 %4, %4, %5, %6\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %2, %7\n\t"
+      "s_nop 1"
+      : "+&v"(a0), "+&v"(a1), "+&v"(c0), "+&v"(c1), "+&v"(q0), "+&v"(q1)
+      : "s"(kLaneBit1), "s"(kLaneBit0));
+  return sum_bit4(a0, q0);
+}
+
+__device__ __forceinline__ float sum_y(float a0, float a1, float c0, float c1, float q0, float q1, float n) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_e64 %0, %0, %1, %7\n\t"
+      "v_cndmask_b32_e64 %2, %2, %3, %7\n\t"
+      "v_cndmask_b32_e64 %4, %4, %5, %7\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_cndmask_b32_e64 %0, %0, %2, %8\n\t"
+      "v_cndmask_b32_e64 %4, %4, %6, %8\n\t"
+      "s_nop 1"
+      : "+&v"(a0), "+&v"(a1), "+&v"(c0), "+&v"(c1), "+&v"(q0), "+&v"(q1), "+&v"(n)
+      : "s"(kLaneBit1), "s"(kLaneBit0));
+  return sum_bit4(a0, q0);
 }
 
 __device__ __forceinline__ int wave_max_int(int v) {

@@ -20,6 +20,11 @@
 // (Both halves in the forward too, with eight waves of 8x4 pixels per tile, cut the longest tile's
 // walk to 97 + 157 ns per face, but twice the waves with their set-up and hit masks, and 1.4 times
 // the gradient atomics, made every case slower: mapping 2.53 ms.)
+//   Where lists are short (the 8-view window: 42 faces a tile, 12 visits a wave) a quarter of the
+// fused kernel's VALU instructions were outside the walks: 1,809 a wave, 462 of them in the set-up,
+// the hit masks, the seeds and the wave maximum.  The backward takes the masks that the forward
+// formed for the span still in LDS, the seeds' scales come from the host, the maximum goes by
+// DPP: window 629 -> 616 us, 640x480 tracking 542 -> 533 us for eight iterations.
 #include "tsr_internal.h"
 
 namespace tsr {
@@ -392,7 +397,8 @@ template <int SM, bool COOP, int SPAN = kSpan>
 __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __restrict__ records,
                                              const uint64_t* __restrict__ pairs, float sigma, float t_min,
                                              float4* srec, uint32_t* sface, FwdState& s,
-                                             const NormalIn* nin = nullptr, float4* snrm = nullptr) {
+                                             const NormalIn* nin = nullptr, float4* snrm = nullptr,
+                                             unsigned long long* hits = nullptr) {
   s.T = c.inside ? 1.f : 0.f;
   s.C0 = s.C1 = s.C2 = s.D = 0.f; s.Tb = 1.f; s.last = -1;
   s.N0 = s.N1 = s.N2 = 0.f;
@@ -416,6 +422,7 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
     const float4* sr = srec + h / kBatch * kBatchVec;
     const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
     unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by);
+    if (hits) hits[h / kBatch] = mask;
     if (mask == 0ull) continue;
     auto visit = [&](const Rec& rc, int j) {
       PixelEval e;
@@ -512,26 +519,24 @@ template <int SM>
 __device__ __forceinline__ GradLane grad_lane(acc_t* grad_acc, float* sig_acc, float* persp_acc, float* gacc,
                                               int64_t moff) {
   const int lane = threadIdx.x & 63;
-  const int b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1;
+  const bool b0 = lane & 1, b4 = lane & 16;
+  const int i = 2 * (lane & 2) + ((lane >> 1) & 2) + ((lane >> 3) & 1);      // the lane's value of p0
+  static_assert(kGEdge == 0 && kGCol == 9 && kGOpa == 18 && kGZ == 19, "three terms each of the edges, then of the colours");
   int k = -1, where = 0;      // where: 0 gradient accumulator, 1 exponent, 2 W plane, 3 normal
-  const int i = 4 * b1 + 2 * b2 + b3;                // the lane's value of p0
-  if (!b4 && !b0) {
-    k = i < 3 ? kGEdge + 3 * i + 2 : (i < 6 ? kGCol + 3 * (i - 3) + 2 : (i == 6 ? (int)kGOpa : (int)kGZ));
-  } else if (!b4) {
-    if (i < 6) {
-      k = i < 3 ? kGEdge + 3 * i : kGCol + 3 * (i - 3);
-    } else if (i == 6 && p1_terms<SM>() == 7) {
-      where = persp_mode<SM>() ? 2 : 1;
-      k = 0;
-    }
-  } else if (!b0) {
-    if (i < 6) {
-      k = i < 3 ? kGEdge + 3 * i + 1 : kGCol + 3 * (i - 3) + 1;
-    } else if (persp_mode<SM>() && i == 7) {
-      where = 2;
-      k = 1;
-    }
-  } else if (normal_mode<SM>() && i < 3) {
+  if (i < 6) {
+    if (!(b0 && b4)) k = 3 * i + (b4 ? 1 : (b0 ? 0 : 2));
+  } else if (!b0 && !b4) {
+    k = 12 + i;
+  }
+  if (p1_terms<SM>() == 7 && i == 6 && b0 && !b4) {
+    where = persp_mode<SM>() ? 2 : 1;
+    k = 0;
+  }
+  if (persp_mode<SM>() && i == 7 && !b0 && b4) {
+    where = 2;
+    k = 1;
+  }
+  if (normal_mode<SM>() && i < 3 && b0 && b4) {
     where = 3;
     k = i;
   }
@@ -580,10 +585,11 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
                                               const PixGrad& pg, float4* srec, uint32_t* sface, int* sint,
                                               acc_t* __restrict__ grad_acc, float* __restrict__ sig_acc,
                                               float* __restrict__ persp_acc, const NormalIn* nin = nullptr,
-                                              float4* snrm = nullptr, uint32_t staged = ~0u) {
+                                              float4* snrm = nullptr, uint32_t staged = ~0u,
+                                              const unsigned long long* hits = nullptr) {
   const int lane = threadIdx.x & 63;
   // highest list position any pixel of this wave (COOP: of the workgroup) blended
-  const int wlast = uniform_int(wave_max_int(last));
+  const int wlast = wave_max_int(last);
   constexpr int kStage = COOP ? SPAN : kBatch;      // faces staged at once
   int top = wlast;
   if (COOP && c.end - c.start <= (uint32_t)kStage) {
@@ -628,7 +634,8 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
     // cooperative spans start where the forward's do, so that the last one it staged is still there
     s0 = COOP ? (int)c.start + (s1 - 1 - (int)c.start) / kStage * kStage : max((int)c.start, s1 - kStage);
     const int ns = s1 - s0;
-    if (!COOP || (uint32_t)s0 != staged) {
+    const bool kept = COOP && (uint32_t)s0 == staged;      // the forward's last span, with its masks
+    if (!kept) {
       if constexpr (COOP) __syncthreads();
       stage_span<SM, COOP>(records, pairs, (uint32_t)s0, ns, srec, sface, nin, c.view, snrm);
     }
@@ -639,7 +646,8 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
     const float4* sr = srec + h / kBatch * kBatchVec;
     const uint32_t* sf = sface + h / kBatch * kSlots;
     const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
-    unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by);
+    // (a batch at or before the wave's last face is one whose mask its forward formed)
+    unsigned long long mask = kept ? uniform_u64(hits[h / kBatch]) : batch_hit_mask<SM>(sr, n, c.bx, c.by);
     if (wlast - b0 < 63) mask &= (2ull << (wlast - b0)) - 1ull;     // faces after the wave's last
     if (mask == 0ull) continue;
     int j0 = last_bit(mask), j1 = last_bit(mask);
@@ -894,6 +902,12 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const flo
   }
 }
 
+// Per-view scale of the L1 seeds (eqs. 8-10): w_color / (3 W H) and w_depth / (W H), formed on the host
+// (two IEEE divisions are 20 instructions of every wave).
+struct SeedScale {
+  float c[TSR_MAX_VIEWS], d[TSR_MAX_VIEWS];
+};
+
 // Fused training kernel: forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
 // images and runs in tsr_ssim.hip between a separate forward and backward), backward
 // walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant).
@@ -902,9 +916,8 @@ template <int SM>
 __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
                                                         const uint64_t* __restrict__ pairs,
                                                         const uint32_t* __restrict__ ranges, float sigma, float t_min,
-                                                        float w_color, float w_depth,
-                                                        const float* __restrict__ tcolor, const float* __restrict__ tdepth,
-                                                        float* __restrict__ color, float* __restrict__ depth,
+                                                        SeedScale scale, const float* __restrict__ tcolor,
+                                                        const float* __restrict__ tdepth, float* __restrict__ color, float* __restrict__ depth,
                                                         float* __restrict__ trans, float* __restrict__ loss_part,
                                                         acc_t* __restrict__ grad_acc, float* __restrict__ sig_acc,
                                                         float* __restrict__ persp_acc,
@@ -913,6 +926,7 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
   // the four waves stage each span together (one copy of the records per tile)
   __shared__ float4 srec[span_batches(kSpan) * kBatchVec];
   __shared__ uint32_t sface[span_batches(kSpan) * kSlots];
+  __shared__ unsigned long long s_hits[kWaves][span_batches(kSpan)];
   __shared__ int s_item;
   __shared__ int sint[4];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -957,19 +971,20 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       td = tdepth[c.pix];
     }
     FwdState s;
-    forward_walk<SM, true>(c, records, pairs, sigma, t_min, srec, sface, s);
+    forward_walk<SM, true>(c, records, pairs, sigma, t_min, srec, sface, s, nullptr, nullptr, s_hits[wv]);
     PixGrad pg{0.f, 0.f, 0.f, 0.f, 0.f};
     float lpix = 0.f;
     if (c.inside) {
-      const float inv_c = w_color / (3.f * (float)hw), inv_d = w_depth / (float)hw;
+      const float inv_c = scale.c[c.view], inv_d = scale.d[c.view];
       const float r0 = s.C0 - t0, r1 = s.C1 - t1, r2 = s.C2 - t2;
       const float rd = s.D - td;
-      const float md = td > 0.f ? 1.f : 0.f;
-      pg.g0 = inv_c * (float)((r0 > 0.f) - (r0 < 0.f));
-      pg.g1 = inv_c * (float)((r1 > 0.f) - (r1 < 0.f));
-      pg.g2 = inv_c * (float)((r2 > 0.f) - (r2 < 0.f));
-      pg.gd = md * inv_d * (float)((rd > 0.f) - (rd < 0.f));
-      lpix = inv_c * (fabsf(r0) + fabsf(r1) + fabsf(r2)) + md * inv_d * fabsf(rd);
+      const float md = td > 0.f ? inv_d : 0.f;
+      auto signed_scale = [](float r, float k) { return r > 0.f ? k : (r < 0.f ? -k : 0.f); };
+      pg.g0 = signed_scale(r0, inv_c);
+      pg.g1 = signed_scale(r1, inv_c);
+      pg.g2 = signed_scale(r2, inv_c);
+      pg.gd = signed_scale(rd, md);
+      lpix = inv_c * (fabsf(r0) + fabsf(r1) + fabsf(r2)) + md * fabsf(rd);
       if (color) {
         float* cb = color + 3 * c.vd.pix_off + off;
         cb[0] = s.C0;
@@ -985,7 +1000,7 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       if (lane == 0) loss_part[kWaves * tile + quad] = ws;
     }
     backward_walk<SM, true>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
-                            persp_acc, nullptr, nullptr, s.staged);
+                            persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
     if (!persistent) break;
   }
 }
@@ -1821,7 +1836,14 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
     dim3 grid(tile_grid(vt.n_tiles));
     if (sched.order && !sched.persistent) grid = dim3(vt.n_tiles);
     if (sched.persistent) grid = dim3(sched.grid > 0 ? sched.grid : 2048);
-#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", k_train_fused<S>, grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, p.w_color, p.w_depth, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
+    SeedScale scale;
+    for (int v = 0; v < vt.n_views; ++v) {
+      const float hw = (float)((int64_t)vt.v[v].width * vt.v[v].height);
+      scale.c[v] = p.w_color / (3.f * hw);
+      scale.d[v] = p.w_depth / hw;
+    }
+    for (int v = vt.n_views; v < TSR_MAX_VIEWS; ++v) scale.c[v] = scale.d[v] = 0.f;
+#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", k_train_fused<S>, grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
     TSR_MODE_SWITCH(sm, TSR_TRAIN)
 #undef TSR_TRAIN
   }

@@ -77,7 +77,7 @@ __device__ __forceinline__ int view_of_tile(const ViewTable& vt, int tile) {
   int v = 0;
   for (int i0 = 0; i0 < vt.n_views; i0 += 8) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v += tile >= vt.v[i0 + i].tile_off ? 1 : 0;
+    for (int i = 0; i < 8; ++i) v += (int)((uint32_t)(vt.v[i0 + i].tile_off - 1 - tile) >> 31);   // tile >= tile_off
   }
   return v - 1;
 }
@@ -255,12 +255,25 @@ __device__ __forceinline__ float sum_y(float a0, float a1, float c0, float c1, f
   return sum_bit4(a0, q0);
 }
 
+// Largest value of the wave, in every lane (row-wise DPP steps and broadcasts, no LDS).
 __device__ __forceinline__ int wave_max_int(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  return v;
+#define TSR_DPP_MAX(ctrl, rmask) v = max(v, __builtin_amdgcn_update_dpp(v, v, ctrl, rmask, 0xF, false))
+  TSR_DPP_MAX(0xB1, 0xF);      // quad_perm [1,0,3,2]
+  TSR_DPP_MAX(0x4E, 0xF);      // quad_perm [2,3,0,1]
+  TSR_DPP_MAX(0x124, 0xF);     // row_ror:4
+  TSR_DPP_MAX(0x128, 0xF);     // row_ror:8
+  TSR_DPP_MAX(0x142, 0xA);     // row_bcast:15 into rows 1 and 3
+  TSR_DPP_MAX(0x143, 0xC);     // row_bcast:31 into rows 2 and 3
+#undef TSR_DPP_MAX
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return ((unsigned long long)hi << 32) | lo;
+}
 
 // Wave ballot of a predicate, taken as a lane mask directly (no conversion to an integer first).
 __device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }

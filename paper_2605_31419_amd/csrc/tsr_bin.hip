@@ -846,25 +846,6 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ range
 // ---------------------------------------------------------------------------- per-tile sort
 constexpr int kSortLds = 4096;     // keys sorted in one LDS pass (32 KiB)
 
-__device__ __forceinline__ void bitonic_lds(uint64_t* s, int n2) {
-  for (int k = 2; k <= n2; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-        const int ixj = i ^ j;
-        if (ixj > i) {
-          const uint64_t a = s[i], b = s[ixj];
-          const bool up = (i & k) == 0;
-          if ((a > b) == up) {
-            s[i] = b;
-            s[ixj] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
 __device__ __forceinline__ int lower_bound_u64(const uint64_t* a, int n, uint64_t x) {
   int lo = 0, hi = n;
   while (lo < hi) {
@@ -1002,14 +983,75 @@ __device__ __forceinline__ void wave_sort_tile(uint64_t* base, int n) {
     if (lane * R + r < n) base[lane * R + r] = k[r];
 }
 
+// Sort of n <= 256 K keys at base by one workgroup of 256 threads: runs of 512 keys sorted in
+// registers, one wave a run, then merged pairwise in LDS.  A key's place in a merged pair is its index
+// in its run plus its rank in the other one (a binary search; the keys are unique); a thread's K keys
+// wait in registers while the places are found, so the merges need no second buffer, and their K
+// searches are independent, which hides the LDS latency that a search is made of.  (With a bitonic
+// network over the whole list, in LDS, each of its 78 stages for 4096 keys waited on a barrier: the
+// sorts of a batch of eight mixed views took 97 us for the longest lists' sake, 53 now.)
+template <int K>
+__device__ __forceinline__ void block_merge_sort(uint64_t* base, int n, uint64_t* s) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  constexpr int R = 8, C = 64 * R;
+  static_assert(256 * K <= kSortLds, "the list fits the LDS buffer");
+  for (int run = tid >> 6; run * C < n; run += 4) {
+    uint64_t k[R];
+    const int i0 = run * C + lane * R;
+#pragma unroll
+    for (int r = 0; r < R; ++r) k[r] = i0 + r < n ? base[i0 + r] : ~0ull;
+    wave_bitonic<R>(k);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (i0 + r < n) s[i0 + r] = k[r];
+  }
+  __syncthreads();
+  if (n <= C) {                            // one run: no merge writes it out
+    for (int i = tid; i < n; i += 256) base[i] = s[i];
+    __syncthreads();
+    return;
+  }
+  static_assert(C >= 256, "a thread's key r is in the run of key r * 256, whatever the thread");
+  for (int sh = 31 - __builtin_clz(C); (1 << sh) < n; ++sh) {      // merge runs of w = 2^sh keys
+    const int w = 1 << sh;
+    uint64_t key[K];
+    int pos[K];                            // the key's rank in the partner run
+    auto other = [&](int r) { return ((r * 256 >> sh) ^ 1) << sh; };       // start of the partner run
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      key[r] = r * 256 + tid < n ? s[r * 256 + tid] : 0ull;                // (no key is below 0)
+      pos[r] = 0;
+    }
+    for (int st = w; st > 0; st >>= 1) {
+#pragma unroll
+      for (int r = 0; r < K; ++r) {
+        const int o = other(r), q = pos[r] + st;
+        if (q <= min(w, n - o) && s[o + q - 1] < key[r]) pos[r] = q;
+      }
+    }
+    __syncthreads();
+    const bool last = 2 * w >= n;
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      const int i = r * 256 + tid;
+      if (i >= n) continue;
+      const int at = (i >> (sh + 1) << (sh + 1)) + (i & (w - 1)) + pos[r];
+      if (last) base[at] = key[r];
+      else s[at] = key[r];
+    }
+    __syncthreads();
+  }
+}
+
 // Per-tile depth sort, ascending by (z bits, face), in one launch with two kinds of
 // workgroups: the first kLongBlocks are persistent over the list of tiles longer than
 // kWaveSortMax keys (built by k_scan_tiles), so they start first and overlap the rest; each
 // remaining workgroup sorts four tiles, one wave each, in registers.
 //   Long lists of up to kRegSortMax keys are sorted in registers by the whole workgroup
-// (block_bitonic1024); up to kSortLds keys are bitonic-sorted in LDS; longer ones are sorted
-// in LDS-sized chunks and merged pairwise in global memory through `temp` (keys are unique,
-// so a rank by binary search places every key).
+// (block_bitonic1024: 11.6 us for the launch at 1200x680 with 1M faces, whose longest list has 594
+// keys, against 13.3 by merged runs); up to kSortLds keys by block_merge_sort; longer ones in chunks of that
+// size that are merged pairwise in global memory through `temp` (keys are unique, so a rank by
+// binary search places every key).
 constexpr int kLongBlocks = 64;
 
 __device__ __forceinline__ void sort_long_tiles(const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ long_cnt,
@@ -1034,13 +1076,8 @@ __device__ __forceinline__ void sort_long_tiles(const uint32_t* __restrict__ ran
   }
   for (int c0 = 0; c0 < n; c0 += kSortLds) {
     const int cn = min(kSortLds, n - c0);
-    int n2 = 1;
-    while (n2 < cn) n2 <<= 1;
-    for (int i = threadIdx.x; i < n2; i += blockDim.x) s[i] = i < cn ? base[c0 + i] : ~0ull;
-    __syncthreads();
-    bitonic_lds(s, n2);
-    for (int i = threadIdx.x; i < cn; i += blockDim.x) base[c0 + i] = s[i];
-    __syncthreads();
+    if (cn <= 2048) block_merge_sort<8>(base + c0, cn, s);
+    else block_merge_sort<16>(base + c0, cn, s);
   }
   if (n <= kSortLds) continue;
   uint64_t* src = base;

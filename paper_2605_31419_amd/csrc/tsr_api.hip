@@ -143,7 +143,7 @@ WsLayout layout(const ViewTable& vt, int64_t cap) {
   o = 256;
   L.pose_acc = o; o = align_up(o + sizeof(double) * tsr::kSumCopies * 6 * vt.n_views);
   L.loss_acc = o; o = align_up(o + sizeof(double) * tsr::kSumCopies * vt.n_views);
-  L.loss_part = o; o = align_up(o + sizeof(float) * 4 * vt.n_tiles);
+  L.loss_part = o; o = align_up(o + sizeof(float) * tsr::kTileParts * vt.n_tiles);
   L.counts = o; o = align_up(o + sizeof(uint32_t) * nf);
   L.records = o; o = align_up(o + sizeof(float) * tsr::kRecDwords * nf);
   L.grad_acc = o; o = align_up(o + sizeof(tsr::acc_t) * tsr::kGradDwords * nf);

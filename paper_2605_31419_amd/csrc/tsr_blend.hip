@@ -50,14 +50,56 @@ __device__ __forceinline__ int tile_of_block(int n_tiles) {
   return (idx < per && t < n_tiles) ? t : -1;
 }
 
-// Tile of a one-workgroup-per-tile launch: the longest-first order when one is given (the
-// permutation of the tile ids built with the binning; an entry outside [0, n_tiles) gives no
-// tile), else the XCD-interleaved id order.
-__device__ __forceinline__ int tile_of_block_ordered(int n_tiles, const int* __restrict__ order) {
-  if (!order) return tile_of_block(n_tiles);
-  if ((int)blockIdx.x >= n_tiles) return -1;
-  const int t = order[blockIdx.x];
-  return (t >= 0 && t < n_tiles) ? t : -1;
+// What a workgroup walks: a tile, or the left or right half of a split one.
+struct Item {
+  int tile;              // -1: nothing
+  int half;
+  bool split;
+};
+
+// Long tiles are split between two workgroups: wave w then owns the left or right 8x4 half (four
+// columns, eight rows) of its quadrant, one pixel a lane of each half of the wave, so that both walks
+// take two faces per round at half the pixels' work.  A round's latency is what the longest tile costs,
+// and a split tile's is 0.6 to 0.7 of a whole one's; its work is 1.2 times as much.  So a tile is split
+// only where its own walk would outlast the launch: a listed face costs the tile 0.34 us, and the whole
+// card about 0.22 ns, so from K / kSplitDiv listed faces on (K: pairs of the binning), and from
+// kSplitMin on, below which nothing is to be gained.  That does not happen to several views, whose
+// kernels are built without the split walks (their registers cost the 8-view window 2 %), and the few
+// workgroups of a small image gain nothing and wait for the larger kernel's instructions (64x48: the
+// step 45.4 -> 47.0 us).
+// One 1200x680 view of 1M faces: forward 73 -> 55 us, backward 128 -> 117, fused 161 -> 139, face
+// statistics 61 -> 48.
+constexpr int kSplitMax = 256;           // split tiles at most: the first of the longest-first order
+constexpr uint32_t kSplitDiv = 1536, kSplitMin = 128;
+constexpr int kSplitTiles = 128;         // tiles of the view from which on tiles are split
+
+static __host__ __device__ inline int split_items(const ViewTable& vt) {
+  return vt.n_views == 1 && vt.n_tiles >= kSplitTiles ? min(kSplitMax, vt.n_tiles / 8) : 0;
+}
+
+// Item i of a launch (ONE: of a single view): without an order the XCD-interleaved tile ids (i: the workgroup); with the
+// longest-first order (the permutation of the tile ids built with the binning; an entry outside
+// [0, n_tiles) gives no tile) first the second halves of its first split_items tiles (none
+// where the tile is not split), then every tile, whole or its first half.
+template <bool ONE>
+__device__ __forceinline__ Item item_at(int i, const ViewTable& vt, const int* __restrict__ order,
+                                        const uint32_t* __restrict__ ranges) {
+  Item it{-1, 0, false};
+  const int n_tiles = vt.n_tiles, ns = ONE ? split_items(vt) : 0;
+  const int pos = i < ns ? i : i - ns;
+  if (pos >= n_tiles) return it;
+  const int t = order[pos];
+  if (t < 0 || t >= n_tiles) return it;
+  if (pos < ns) it.split = ranges[2 * t + 1] - ranges[2 * t] > max(kSplitMin, ranges[2 * n_tiles - 1] / kSplitDiv);
+  it.half = i < ns ? 1 : 0;
+  if (it.half == 0 || it.split) it.tile = t;
+  return it;
+}
+
+template <bool ONE>
+__device__ __forceinline__ Item item_of_block(const ViewTable& vt, const int* __restrict__ order,
+                                              const uint32_t* __restrict__ ranges) {
+  return order ? item_at<ONE>((int)blockIdx.x, vt, order, ranges) : Item{tile_of_block(vt.n_tiles), 0, false};
 }
 
 // Kernel modes: the low three bits select the window exponent -- 1: sigma = 1, 2: sigma = 0.5,
@@ -175,15 +217,22 @@ __device__ __forceinline__ bool eval_face(const Rec& rc, float dx, float dy, flo
 struct TileCtx {
   int tile, view;
   ViewDesc vd;
-  int bx, by;            // top-left pixel of this wave's 8x8 quadrant
+  int bx, by;            // top-left pixel of this wave's 8x8 quadrant, or of its half of a split tile
+  int bw;                // width of that box
+  bool own;              // the pixel is inside the image and this lane is the one that writes it
   int px, py;
   bool inside;
   int64_t pix;           // packed pixel index (valid when inside)
   uint32_t start, end;   // tile list range
 };
 
-__device__ __forceinline__ void tile_ctx(const ViewTable& vt, const uint32_t* __restrict__ ranges, int tile,
-                                         int quad, TileCtx& c) {
+// The pixel of a lane in the walks' two-face layout: lane bits 2 and 3 are x, bits 0, 1 and 4 y.
+__device__ __forceinline__ int lane_x(int lane) { return (lane >> 2) & 3; }
+__device__ __forceinline__ int lane_y(int lane) { return (lane & 3) | ((lane >> 2) & 4); }
+
+__device__ __forceinline__ void tile_ctx(const ViewTable& vt, const uint32_t* __restrict__ ranges, const Item& it, int quad,
+                                         TileCtx& c) {
+  const int tile = it.tile;
   c.tile = tile;
   c.view = view_of_tile(vt, tile);
   c.vd = vt.v[c.view];
@@ -192,9 +241,17 @@ __device__ __forceinline__ void tile_ctx(const ViewTable& vt, const uint32_t* __
   const int lane = threadIdx.x & 63;
   c.bx = tx * kTile + (quad & 1) * 8;
   c.by = ty * kTile + (quad >> 1) * 8;
-  c.px = c.bx + (lane & 7);
-  c.py = c.by + (lane >> 3);
+  c.bw = it.split ? 4 : 8;
+  if (it.split) {                        // (every pixel in both halves of the wave)
+    c.bx += 4 * it.half;
+    c.px = c.bx + lane_x(lane);
+    c.py = c.by + lane_y(lane);
+  } else {
+    c.px = c.bx + (lane & 7);
+    c.py = c.by + (lane >> 3);
+  }
   c.inside = c.px < c.vd.width && c.py < c.vd.height;
+  c.own = c.inside && !(it.split && lane >= kWave / 2);
   c.pix = c.vd.pix_off + (int64_t)c.py * c.vd.width + c.px;
   c.start = ranges[2 * tile];
   c.end = ranges[2 * tile + 1];
@@ -238,7 +295,7 @@ static_assert(span_batches(kSpan) * (kBatchVec * sizeof(float4) + kSlots * sizeo
               "a staged span fits the LDS budget");
 static_assert(kWaves * kWave == kBlock && kWaves == 4, "one wave per 8x8 quadrant of a 16x16 tile");
 static_assert(kGradDwords == 20, "the accumulator row that grad_lane addresses");
-static_assert(kWaves == kTileQuads, "normal-loss sums: one slot per wave of a tile");
+static_assert(2 * kWaves == kTileParts, "loss sums: two slots per wave of a tile");
 
 // One wave stages a batch: lane l takes face l's id, then its record in kRecParts loads that go
 // straight from memory to LDS (no registers, all in flight at once), and with the normal channels
@@ -303,7 +360,7 @@ __device__ __forceinline__ void load_edges(const float4* srec, int j, float (&r)
 }
 
 template <int SM>
-__device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec, int n, int bx, int by) {
+__device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec, int n, int bx, int by, int bw) {
   const int j = threadIdx.x & 63;
   bool hit = false;
   if constexpr (persp_mode<SM>()) {
@@ -311,7 +368,7 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
       const float4 rc = srec[kRecU0 / 4 * kSlots + j];
       float r[12];
       load_edges(srec, j, r);
-      const float dxl = (float)bx - rc.x, dxh = (float)(bx + 7) - rc.x;
+      const float dxl = (float)bx - rc.x, dxh = (float)(bx + bw - 1) - rc.x;
       const float dyl = (float)by - rc.y, dyh = (float)(by + 7) - rc.y;
       const float mx = fmaxf(fabsf(dxl), fabsf(dxh)), my = fmaxf(fabsf(dyl), fabsf(dyh));
       hit = true;
@@ -330,7 +387,7 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
     const float4 rc = srec[kRecU0 / 4 * kSlots + j];
     const int u1v1 = __float_as_int(rc.z);
     const int u0 = (int)rc.x, v0 = (int)rc.y, u1 = u1v1 & 0xffff, v1 = u1v1 >> 16;
-    const int xl = max(bx, u0), xh = min(bx + 7, u1), yl = max(by, v0), yh = min(by + 7, v1);
+    const int xl = max(bx, u0), xh = min(bx + bw - 1, u1), yl = max(by, v0), yh = min(by + 7, v1);
     hit = xl <= xh && yl <= yh;
     if (hit) {
       float r[12];
@@ -393,7 +450,7 @@ __device__ __forceinline__ int last_bit(unsigned long long& mask) {
 // record is loaded from LDS a face ahead, while the other one of the pair is evaluated and
 // blended: a wave alone issues one instruction in about five cycles and waits 130 for a record,
 // and the waves of the longest tiles bound the kernel.
-template <int SM, bool COOP, int SPAN = kSpan>
+template <int SM, bool COOP, bool SPLIT, int SPAN = kSpan>
 __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __restrict__ records,
                                              const uint64_t* __restrict__ pairs, float sigma, float t_min,
                                              float4* srec, uint32_t* sface, FwdState& s,
@@ -403,6 +460,7 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
   s.C0 = s.C1 = s.C2 = s.D = 0.f; s.Tb = 1.f; s.last = -1;
   s.N0 = s.N1 = s.N2 = 0.f;
   s.staged = ~0u;
+  const bool upper = (threadIdx.x & 63) >= kWave / 2;
   const float dxb = (float)c.px, dyb = (float)c.py;
   constexpr int kStage = COOP ? SPAN : kBatch;      // faces staged at once
   for (uint32_t s0 = c.start; s0 < c.end; s0 += kStage) {
@@ -421,51 +479,107 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
     const uint32_t b0 = s0 + (uint32_t)h;
     const float4* sr = srec + h / kBatch * kBatchVec;
     const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
-    unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by);
+    unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by, c.bw);
     if (hits) hits[h / kBatch] = mask;
     if (mask == 0ull) continue;
-    auto visit = [&](const Rec& rc, int j) {
-      PixelEval e;
-      // stopping also at T == 0 means the backward never divides by 1 - alpha = 0
-      const bool act = eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e) && lv;
-      // lanes that do not blend this face keep their state: alpha 0 gives weight 0 and T * 1
-      const float a = act ? e.alpha : 0.f;
-      const float w = a * s.T;
-      s.C0 = fmaf(e.c0, w, s.C0);
-      s.C1 = fmaf(e.c1, w, s.C1);
-      s.C2 = fmaf(e.c2, w, s.C2);
-      s.D = fmaf(e.zp, w, s.D);
-      if constexpr (normal_mode<SM>()) {
-        const float4 nf = sn[j];
-        s.N0 = fmaf(nf.x, w, s.N0);
-        s.N1 = fmaf(nf.y, w, s.N1);
-        s.N2 = fmaf(nf.z, w, s.N2);
+    if constexpr (SPLIT) {
+      // a face per half of the wave; its alpha and channels to both halves (the first and third, second
+      // and depth of each face side by side), blended in order there
+      int j0 = first_bit(mask), j1 = first_bit(mask);
+      int jl = upper ? j1 : j0;
+      Rec rc;
+      load_rec(sr, jl, rc);
+      for (;;) {
+        const int i0 = (int)b0 + j0, i1 = (int)b0 + j1;
+        PixelEval e;
+        eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e);
+        const Halves A = swap_halves(fmaxf(e.alpha, 0.f), fmaxf(e.alpha, 0.f));
+        const Halves X = swap_halves(e.c0, e.c2), Y = swap_halves(e.c1, e.zp);
+        Halves NX{0.f, 0.f}, NY{0.f, 0.f};
+        if constexpr (normal_mode<SM>()) {
+          const float4 nf = sn[jl];
+          NX = swap_halves(nf.x, nf.z);
+          NY = swap_halves(nf.y, nf.y);
+        }
+        j0 = first_bit(mask);
+        j1 = first_bit(mask);
+        jl = upper ? j1 : j0;
+        __builtin_amdgcn_sched_barrier(0);
+        load_rec(sr, jl, rc);
+        __builtin_amdgcn_sched_barrier(0);
+        auto blend = [&](float alpha, float x, float y, float nx, float ny, int i) {
+          const float a = lv ? alpha : 0.f;
+          const bool act = a > 0.f;
+          const float w = a * s.T;
+          s.C0 = fmaf(x, w, s.C0);       // (C0 | C2)
+          s.C1 = fmaf(y, w, s.C1);       // (C1 | D)
+          if constexpr (normal_mode<SM>()) {
+            s.N0 = fmaf(nx, w, s.N0);    // (N0 | N2)
+            s.N1 = fmaf(ny, w, s.N1);
+          }
+          s.Tb = act ? s.T : s.Tb;
+          s.last = act ? i : s.last;
+          s.T = s.T * (1.f - a);
+          lv = live(s.T, t_min);
+        };
+        blend(A.f0, X.f0, Y.f0, NX.f0, NY.f0, i0);
+        blend(A.f1, X.f1, Y.f1, NX.f1, NY.f1, i1);
+        const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
+        if (done) break;
       }
-      s.Tb = act ? s.T : s.Tb;
-      s.last = act ? (int)(b0 + j) : s.last;
-      s.T = s.T * (1.f - a);
-      lv = live(s.T, t_min);
-    };
-    int j0 = first_bit(mask);
-    int j1 = first_bit(mask);
-    Rec r0, r1;
-    load_rec(sr, j0, r0);
-    load_rec(sr, j1, r1);
-    for (;;) {
-      visit(r0, j0);
-      j0 = first_bit(mask);
-      __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
+    } else {
+      auto visit = [&](const Rec& rc, int j) {
+        PixelEval e;
+        // stopping also at T == 0 means the backward never divides by 1 - alpha = 0
+        const bool act = eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e) && lv;
+        // lanes that do not blend this face keep their state: alpha 0 gives weight 0 and T * 1
+        const float a = act ? e.alpha : 0.f;
+        const float w = a * s.T;
+        s.C0 = fmaf(e.c0, w, s.C0);
+        s.C1 = fmaf(e.c1, w, s.C1);
+        s.C2 = fmaf(e.c2, w, s.C2);
+        s.D = fmaf(e.zp, w, s.D);
+        if constexpr (normal_mode<SM>()) {
+          const float4 nf = sn[j];
+          s.N0 = fmaf(nf.x, w, s.N0);
+          s.N1 = fmaf(nf.y, w, s.N1);
+          s.N2 = fmaf(nf.z, w, s.N2);
+        }
+        s.Tb = act ? s.T : s.Tb;
+        s.last = act ? (int)(b0 + j) : s.last;
+        s.T = s.T * (1.f - a);
+        lv = live(s.T, t_min);
+      };
+      int j0 = first_bit(mask);
+      int j1 = first_bit(mask);
+      Rec r0, r1;
       load_rec(sr, j0, r0);
-      __builtin_amdgcn_sched_barrier(0);
-      visit(r1, j1);
-      j1 = first_bit(mask);
-      __builtin_amdgcn_sched_barrier(0);
       load_rec(sr, j1, r1);
-      __builtin_amdgcn_sched_barrier(0);
-      const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
-      if (done) break;
+      for (;;) {
+        visit(r0, j0);
+        j0 = first_bit(mask);
+        __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
+        load_rec(sr, j0, r0);
+        __builtin_amdgcn_sched_barrier(0);
+        visit(r1, j1);
+        j1 = first_bit(mask);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rec(sr, j1, r1);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
+        if (done) break;
+      }
     }
     }
+  }
+  if constexpr (SPLIT) {
+    const Halves x = swap_halves(s.C0, s.C0), y = swap_halves(s.C1, s.C1), n = swap_halves(s.N0, s.N0);
+    s.C0 = x.f0;
+    s.C2 = x.f1;
+    s.C1 = y.f0;
+    s.D = y.f1;
+    s.N0 = n.f0;
+    s.N2 = n.f1;
   }
 }
 
@@ -579,7 +693,7 @@ __device__ __forceinline__ void add_total(const GradLane& gl, uint32_t g, float 
 // S = gC.B + gD BD - gT BA, so S is carried instead: with P = gC.c + gD z - gT for the face,
 // dL/dalpha = T (P - S) and S <- alpha P + (1 - alpha) S.  Per-face sums of the 20
 // record-parameter gradients are reduced over the wave and added to grad_acc.
-template <int SM, bool COOP, int SPAN = kSpan>
+template <int SM, bool COOP, bool SPLIT, int SPAN = kSpan>
 __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __restrict__ records,
                                               const uint64_t* __restrict__ pairs, float sigma, int last, float Tb,
                                               const PixGrad& pg, float4* srec, uint32_t* sface, int* sint,
@@ -606,27 +720,34 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
                                     normal_mode<SM>() ? (int64_t)c.view * nin->M : 0);
   // From one pixel per lane to the walk's layout: the lower half of the wave takes the first face of
   // a pair, the upper half the second, each lane two pixels of it, A and B four apart in x.
-  // Lane bits 2 and 3 are x, bits 0, 1 and 4 y.  What is carried from face to face (T, S) is held
-  // once per pixel: of A in the lower half and of B in the upper one.
-  const bool upper = lane >= 32;
-  const int xl = (lane >> 2) & 3, yl = (lane & 3) | ((lane >> 2) & 4);
-  const int la = 8 * yl + xl, lb = la + 4;           // lanes of the pixels before
-  int lastp[2];
-  PixGrad pp[2];
+  // What is carried from face to face (T, S) is held once per pixel: of A in the lower half and of B in
+  // the upper one.  In a split tile a lane has pixel A only, and T and S are held in both halves.
+  constexpr int NP = SPLIT ? 1 : 2;
+  const bool upper = lane >= kWave / 2;
+  const int xl = lane_x(lane), yl = lane_y(lane);
+  int lastp[NP], lastl = last;
+  PixGrad pp[NP];
+  float Tl = Tb;                                     // T before the last blended face
+  if constexpr (SPLIT) {
+    lastp[0] = last;
+    pp[0] = pg;
+  } else {
+    const int la = 8 * yl + xl, lb = la + 4;         // lanes of the pixels before
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int l = q ? lb : la;
-    lastp[q] = __shfl(last, l, 64);
-    pp[q] = PixGrad{__shfl(pg.g0, l, 64), __shfl(pg.g1, l, 64), __shfl(pg.g2, l, 64), __shfl(pg.gd, l, 64),
-                    __shfl(pg.gt, l, 64)};
-    if constexpr (normal_mode<SM>()) {
-      pp[q].gn0 = __shfl(pg.gn0, l, 64);
-      pp[q].gn1 = __shfl(pg.gn1, l, 64);
-      pp[q].gn2 = __shfl(pg.gn2, l, 64);
+    for (int q = 0; q < NP; ++q) {
+      const int l = q ? lb : la;
+      lastp[q] = __shfl(last, l, 64);
+      pp[q] = PixGrad{__shfl(pg.g0, l, 64), __shfl(pg.g1, l, 64), __shfl(pg.g2, l, 64), __shfl(pg.gd, l, 64),
+                      __shfl(pg.gt, l, 64)};
+      if constexpr (normal_mode<SM>()) {
+        pp[q].gn0 = __shfl(pg.gn0, l, 64);
+        pp[q].gn1 = __shfl(pg.gn1, l, 64);
+        pp[q].gn2 = __shfl(pg.gn2, l, 64);
+      }
     }
+    Tl = __shfl(Tb, upper ? lb : la, 64);
+    lastl = upper ? lastp[NP - 1] : lastp[0];
   }
-  const float Tl = __shfl(Tb, upper ? lb : la, 64);  // T before the last blended face
-  const int lastl = upper ? lastp[1] : lastp[0];
   float Tcur = Tl;
   float S = 0.f;
   const float dxb = (float)(c.bx + xl), dyb = (float)(c.by + yl);
@@ -647,7 +768,7 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
     const uint32_t* sf = sface + h / kBatch * kSlots;
     const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
     // (a batch at or before the wave's last face is one whose mask its forward formed)
-    unsigned long long mask = kept ? uniform_u64(hits[h / kBatch]) : batch_hit_mask<SM>(sr, n, c.bx, c.by);
+    unsigned long long mask = kept ? uniform_u64(hits[h / kBatch]) : batch_hit_mask<SM>(sr, n, c.bx, c.by, c.bw);
     if (wlast - b0 < 63) mask &= (2ull << (wlast - b0)) - 1ull;     // faces after the wave's last
     if (mask == 0ull) continue;
     int j0 = last_bit(mask), j1 = last_bit(mask);
@@ -663,11 +784,11 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
       const uint32_t id = sf[jl];
       const float dx = dxb - rc.f[kRecU0], dxB = dx + 4.f;
       const float dy = dyb - rc.f[kRecV0];
-      PixelEval e[2];
-      bool act[2];
-      float alpha[2], P[2];
+      PixelEval e[NP];
+      bool act[NP];
+      float alpha[NP], P[NP];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
+      for (int q = 0; q < NP; ++q) {
         act[q] = eval_face<SM>(rc, q ? dxB : dx, dy, sigma, e[q]) && (il <= lastp[q]);
         alpha[q] = act[q] ? e[q].alpha : 0.f;
         // dL/dalpha = T (gC.(c - B) + gD (z - BD) - gT (1 - BA)) = T (P - S)
@@ -678,7 +799,7 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
         // the face's normal is a colour constant over the face: it enters dL/dalpha like one
         const float4 nf = sn[jl];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) P[q] = fmaf(pp[q].gn0, nf.x, fmaf(pp[q].gn1, nf.y, fmaf(pp[q].gn2, nf.z, P[q])));
+        for (int q = 0; q < NP; ++q) P[q] = fmaf(pp[q].gn0, nf.x, fmaf(pp[q].gn1, nf.y, fmaf(pp[q].gn2, nf.z, P[q])));
       }
       const float opa = rc.f[kRecOpa], sig = face_sigma<SM>(rc.f, sigma);
       j0 = last_bit(mask);
@@ -689,25 +810,32 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
       __builtin_amdgcn_sched_barrier(0);
       // one pixel per lane, both faces: T before each face is the stored value at the last face,
       // else T_after / (1 - alpha), which is T_after itself where the face is not blended (rcp(1) = 1)
-      const Halves ca = swap_halves(alpha[0], alpha[1]), cp = swap_halves(P[0], P[1]);
+      const Halves ca = swap_halves(alpha[0], alpha[NP - 1]), cp = swap_halves(P[0], P[NP - 1]);
       const float om0 = 1.f - ca.f0, om1 = 1.f - ca.f1;
       const float T0 = i0 == lastl ? Tl : Tcur * __builtin_amdgcn_rcpf(om0);
       const float T1 = i1 == lastl ? Tl : T0 * __builtin_amdgcn_rcpf(om1);
       const float S1 = fmaf(ca.f0, cp.f0, om0 * S);
       // and back: one face per lane, both pixels
-      const Halves Tq = swap_halves(T0, T1), Sq = swap_halves(S, S1);
+      Halves Tq, Sq;
+      if constexpr (SPLIT) {
+        Tq.f0 = upper ? T1 : T0;
+        Sq.f0 = upper ? S1 : S;
+      } else {
+        Tq = swap_halves(T0, T1);
+        Sq = swap_halves(S, S1);
+      }
       Tcur = T1;
       S = fmaf(ca.f1, cp.f1, om1 * S1);
       // Sums of the two pixels' terms and of their moments with respect to dx.
       // colour plane gradients: dL/dc_ch(p) = gC_ch alpha T, and c_ch = P dx + Q dy + R
       FaceTerms<SM> ft;
       auto add = [&](int k, float ta, float tb) {
-        ft.p0[k] = ta + tb;
-        if (k < 6) ft.p1[k] = fmaf(tb, dxB, ta * dx);
+        ft.p0[k] = SPLIT ? ta : ta + tb;
+        if (k < 6) ft.p1[k] = SPLIT ? ta * dx : fmaf(tb, dxB, ta * dx);
       };
-      float galpha[2], gc[2][3], gz[2], gk[2][3];
+      float galpha[NP], gc[NP][3], gz[NP], gk[NP][3];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
+      for (int q = 0; q < NP; ++q) {
         const PixGrad& g = pp[q];
         const float Tj = q ? Tq.f1 : Tq.f0;
         galpha[q] = act[q] ? Tj * (P[q] - (q ? Sq.f1 : Sq.f0)) : 0.f;
@@ -747,12 +875,12 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
         }
       }
 #pragma unroll
-      for (int k = 0; k < 3; ++k) add(k, gk[0][k], gk[1][k]);
+      for (int k = 0; k < 3; ++k) add(k, gk[0][k], gk[NP - 1][k]);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) add(3 + k, gc[0][k], gc[1][k]);
-      ft.p0[6] = fmaf(galpha[0], e[0].I, galpha[1] * e[1].I);
-      add(7, gz[0], gz[1]);
-      if constexpr (persp_mode<SM>()) ft.p1[6] = fmaf(gz[1], dxB, gz[0] * dx);
+      for (int k = 0; k < 3; ++k) add(3 + k, gc[0][k], gc[NP - 1][k]);
+      ft.p0[6] = SPLIT ? galpha[0] * e[0].I : fmaf(galpha[0], e[0].I, galpha[NP - 1] * e[NP - 1].I);
+      add(7, gz[0], gz[NP - 1]);
+      if constexpr (persp_mode<SM>()) ft.p1[6] = SPLIT ? gz[0] * dx : fmaf(gz[NP - 1], dxB, gz[0] * dx);
       const float tot = sum_face<SM>(ft, dy);
       // one atomic per lane that holds a total (0 for the empty record)
       if (gl.any) add_total<SM>(gl, id, tot);
@@ -764,7 +892,12 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
 
 // ---------------------------------------------------------------------------- kernels
 
-// COOP: the tile's list is staged cooperatively (one shared copy per workgroup, the four
+// The partial-sum slot of a wave: two per quadrant of a tile (an unsplit tile's wave fills both).
+__device__ __forceinline__ int64_t part_of(const Item& it, int quad) {
+  return 2 * ((int64_t)it.tile * kWaves + quad) + it.half;
+}
+
+// COOP (several views): the tile's list is staged cooperatively (one shared copy per workgroup, the four
 // quadrant waves in step), else per wave (four copies, each wave at its own pace).
 template <int SM, bool COOP>
 __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const float* __restrict__ records,
@@ -775,23 +908,24 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const flo
                                                       float* __restrict__ t_last, const int* __restrict__ order,
                                                       NormalIn nin) {
   const int wv = threadIdx.x >> 6;
-  const int tile = tile_of_block_ordered(vt.n_tiles, order);
-  if (tile < 0) return;
+  const Item it = item_of_block<!COOP>(vt, order, ranges);
+  if (it.tile < 0) return;
   TileCtx c;
-  tile_ctx(vt, ranges, tile, wv, c);
+  tile_ctx(vt, ranges, it, wv, c);
   FwdState s;
   if constexpr (COOP) {
     __shared__ float4 srec[span_batches(kSepSpan) * kBatchVec];
     __shared__ uint32_t sface[span_batches(kSepSpan) * kSlots];
     __shared__ float4 snrm[normal_mode<SM>() ? span_batches(kSepSpan) * kSlots : 1];
     clear_empty_slots(span_batches(kSepSpan), srec, normal_mode<SM>() ? snrm : nullptr, threadIdx.x, kBlock);
-    forward_walk<SM, true, kSepSpan>(c, records, pairs, sigma, t_min, srec, sface, s, &nin, snrm);
+    forward_walk<SM, true, false, kSepSpan>(c, records, pairs, sigma, t_min, srec, sface, s, &nin, snrm);
   } else {
     __shared__ float4 srec[kWaves][kBatchVec];
     __shared__ uint32_t sface[kWaves][kSlots];
     __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kSlots : 1];
     clear_empty_slots(1, srec[wv], normal_mode<SM>() ? snrm[wv] : nullptr, threadIdx.x & 63, kWave);
-    forward_walk<SM, false>(c, records, pairs, sigma, t_min, srec[wv], sface[wv], s, &nin, snrm[wv]);
+    if (it.split) forward_walk<SM, false, true>(c, records, pairs, sigma, t_min, srec[wv], sface[wv], s, &nin, snrm[wv]);
+    else forward_walk<SM, false, false>(c, records, pairs, sigma, t_min, srec[wv], sface[wv], s, &nin, snrm[wv]);
   }
   const int64_t hw = (int64_t)c.vd.width * c.vd.height;
   const int64_t off = (int64_t)c.py * c.vd.width + c.px;
@@ -802,7 +936,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const flo
     const float n1 = R[3] * s.N0 + R[4] * s.N1 + R[5] * s.N2;
     const float n2 = R[6] * s.N0 + R[7] * s.N1 + R[8] * s.N2;
     float cnt = 0.f, l = 0.f, r0 = 0.f, r1 = 0.f, r2 = 0.f;
-    if (c.inside) {
+    if (c.own) {
       const float* tb = nin.target + 3 * c.vd.pix_off + off;
       const float b0 = tb[0], b1 = tb[hw], b2 = tb[2 * hw];
       if (b0 != 0.f || b1 != 0.f || b2 != 0.f) {
@@ -821,12 +955,13 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const flo
     }
     const float tc = wave_sum(cnt), tl = wave_sum(l), t0 = wave_sum(r0), t1 = wave_sum(r1), t2 = wave_sum(r2);
     if ((threadIdx.x & 63) == 0) {
-      float4* pw = reinterpret_cast<float4*>(nin.part + kNormalPart * ((int64_t)tile * kWaves + wv));
+      float4* pw = reinterpret_cast<float4*>(nin.part + kNormalPart * part_of(it, wv));
       pw[0] = make_float4(tc, tl, t0, t1);
       pw[1] = make_float4(t2, 0.f, 0.f, 0.f);
+      if (!it.split) pw[2] = pw[3] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
-  if (!c.inside) return;
+  if (!c.own) return;
   float* cb = color + 3 * c.vd.pix_off + off;
   cb[0] = s.C0;
   cb[hw] = s.C1;
@@ -847,10 +982,10 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const flo
                                                       float* __restrict__ sig_acc, float* __restrict__ persp_acc,
                                                       const int* __restrict__ order, NormalIn nin) {
   const int wv = threadIdx.x >> 6;
-  const int tile = tile_of_block_ordered(vt.n_tiles, order);
-  if (tile < 0) return;
+  const Item it = item_of_block<!COOP>(vt, order, ranges);
+  if (it.tile < 0) return;
   TileCtx c;
-  tile_ctx(vt, ranges, tile, wv, c);
+  tile_ctx(vt, ranges, it, wv, c);
   int last = -1;
   float Tb = 0.f;
   PixGrad pg{0.f, 0.f, 0.f, 0.f, 0.f};
@@ -890,15 +1025,19 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const flo
     __shared__ float4 snrm[normal_mode<SM>() ? span_batches(kSepSpan) * kSlots : 1];
     clear_empty_slots(span_batches(kSepSpan), srec, normal_mode<SM>() ? snrm : nullptr, threadIdx.x, kBlock);
     __shared__ int sint[4];
-    backward_walk<SM, true, kSepSpan>(c, records, pairs, sigma, last, Tb, pg, srec, sface, sint, grad_acc, sig_acc,
-                                      persp_acc, &nin, snrm);
+    backward_walk<SM, true, false, kSepSpan>(c, records, pairs, sigma, last, Tb, pg, srec, sface, sint, grad_acc,
+                                             sig_acc, persp_acc, &nin, snrm);
   } else {
     __shared__ float4 srec[kWaves][kBatchVec];
     __shared__ uint32_t sface[kWaves][kSlots];
     __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kSlots : 1];
     clear_empty_slots(1, srec[wv], normal_mode<SM>() ? snrm[wv] : nullptr, threadIdx.x & 63, kWave);
-    backward_walk<SM, false>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc, sig_acc,
-                             persp_acc, &nin, snrm[wv]);
+    if (it.split)
+      backward_walk<SM, false, true>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc,
+                                     sig_acc, persp_acc, &nin, snrm[wv]);
+    else
+      backward_walk<SM, false, false>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc,
+                                      sig_acc, persp_acc, &nin, snrm[wv]);
   }
 }
 
@@ -908,11 +1047,11 @@ struct SeedScale {
   float c[TSR_MAX_VIEWS], d[TSR_MAX_VIEWS];
 };
 
-// Fused training kernel: forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
+// Fused training kernel (ONE: of a single view that may have split tiles): forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
 // images and runs in tsr_ssim.hip between a separate forward and backward), backward
 // walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant).
 // Five workgroups per CU (96 registers a lane): the records of two faces in flight.
-template <int SM>
+template <int SM, bool ONE>
 __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
                                                         const uint64_t* __restrict__ pairs,
                                                         const uint32_t* __restrict__ ranges, float sigma, float t_min,
@@ -933,10 +1072,10 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
   clear_empty_slots(span_batches(kSpan), srec, nullptr, threadIdx.x, kBlock);
   int round = 0;
   for (;;) {
-    int tile;
+    Item it;
     const int quad = wv;
     if (persistent) {
-      // the workgroup's first tile is its own id; later ones come from the queue (items
+      // the workgroup's first item is its own id; later ones come from the queue (items
       // gridDim.x onward), so the launch does not start with gridDim.x atomics on one address
       int item = (int)blockIdx.x;
       if (round > 0) {
@@ -946,14 +1085,20 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
         item = s_item;
       }
       ++round;
-      if (item >= vt.n_tiles) break;
-      tile = order ? order[item] : item;
+      if (item >= vt.n_tiles + (ONE && order ? split_items(vt) : 0)) break;
+      if constexpr (ONE) {
+        it = order ? item_at<ONE>(item, vt, order, ranges) : Item{item, 0, false};
+        if (it.tile < 0) continue;
+      } else {
+        it = Item{order ? order[item] : item, 0, false};
+      }
     } else {
-      tile = order ? ((int)blockIdx.x < vt.n_tiles ? order[blockIdx.x] : -1) : tile_of_block(vt.n_tiles);
-      if (tile < 0) break;
+      if constexpr (ONE) it = item_of_block<ONE>(vt, order, ranges);
+      else it = Item{order ? order[blockIdx.x] : tile_of_block(vt.n_tiles), 0, false};     // (grid: n_tiles)
+      if (it.tile < 0) break;
     }
     TileCtx c;
-    tile_ctx(vt, ranges, tile, quad, c);
+    tile_ctx(vt, ranges, it, quad, c);
 #if TSR_PRIO_LONG
     // long tile lists bound the kernel's tail: let their waves win issue arbitration
     if (c.end - c.start > TSR_PRIO_LONG) __builtin_amdgcn_s_setprio(2);
@@ -971,7 +1116,10 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       td = tdepth[c.pix];
     }
     FwdState s;
-    forward_walk<SM, true>(c, records, pairs, sigma, t_min, srec, sface, s, nullptr, nullptr, s_hits[wv]);
+    if (ONE && it.split)
+      forward_walk<SM, true, ONE>(c, records, pairs, sigma, t_min, srec, sface, s, nullptr, nullptr, s_hits[wv]);
+    else
+      forward_walk<SM, true, false>(c, records, pairs, sigma, t_min, srec, sface, s, nullptr, nullptr, s_hits[wv]);
     PixGrad pg{0.f, 0.f, 0.f, 0.f, 0.f};
     float lpix = 0.f;
     if (c.inside) {
@@ -984,23 +1132,29 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       pg.g1 = signed_scale(r1, inv_c);
       pg.g2 = signed_scale(r2, inv_c);
       pg.gd = signed_scale(rd, md);
-      lpix = inv_c * (fabsf(r0) + fabsf(r1) + fabsf(r2)) + md * fabsf(rd);
-      if (color) {
+      lpix = !c.own ? 0.f : inv_c * (fabsf(r0) + fabsf(r1) + fabsf(r2)) + md * fabsf(rd);
+      if (color && c.own) {
         float* cb = color + 3 * c.vd.pix_off + off;
         cb[0] = s.C0;
         cb[hw] = s.C1;
         cb[2 * hw] = s.C2;
       }
-      if (depth) depth[c.pix] = s.D;
-      if (trans) trans[c.pix] = s.T;
+      if (depth && c.own) depth[c.pix] = s.D;
+      if (trans && c.own) trans[c.pix] = s.T;
     }
     if (loss_part) {
-      // one plain store per (tile, quadrant); summed per view after the backward
+      // one plain store per (tile, quadrant, half); summed per view after the backward
       const float ws = wave_sum(lpix);
-      if (lane == 0) loss_part[kWaves * tile + quad] = ws;
+      const int part = 2 * (kWaves * it.tile + quad) + it.half;
+      if (lane == 0) loss_part[part] = ws;
+      if (lane == 1 && !it.split) loss_part[part + 1] = 0.f;
     }
-    backward_walk<SM, true>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
-                            persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
+    if (ONE && it.split)
+      backward_walk<SM, true, ONE>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
+                                   persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
+    else
+      backward_walk<SM, true, false>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
+                                     persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
     if (!persistent) break;
   }
 }
@@ -1035,7 +1189,7 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
   for (int k = threadIdx.x; k < TSR_MAX_VIEWS * 6; k += blockDim.x) s_pose[k] = 0.0;
   __syncthreads();
   if (loss_part) {
-    // per-view loss: each thread adds one tile's four quadrant parts; waves whose tiles all
+    // per-view loss: each thread adds one tile's eight parts; waves whose tiles all
     // belong to one view (all but at most one wave per view boundary) add one FP64 atomic
     const int lane = threadIdx.x & 63;
     for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < vt.n_tiles; t0 += (int64_t)gridDim.x * blockDim.x) {
@@ -1043,8 +1197,10 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
       double x = 0.0;
       int v = -1;
       if (t < vt.n_tiles) {
-        const float4 q = reinterpret_cast<const float4*>(loss_part)[t];
-        x = ((double)q.x + (double)q.y) + ((double)q.z + (double)q.w);
+        const float4 q = reinterpret_cast<const float4*>(loss_part)[2 * t];
+        const float4 r = reinterpret_cast<const float4*>(loss_part)[2 * t + 1];
+        x = (((double)q.x + (double)q.y) + ((double)q.z + (double)q.w)) +
+            (((double)r.x + (double)r.y) + ((double)r.z + (double)r.w));
         v = view_of_tile(vt, (int)t);
       }
       const int v0 = __shfl(v, 0, 64);
@@ -1299,8 +1455,8 @@ __device__ void reduce_view_losses(const ViewTable& vt, const float* __restrict_
   __shared__ double red[kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int v = 0; v < vt.n_views; ++v) {
-    const int64_t p0 = (int64_t)kWaves * vt.v[v].tile_off;
-    const int np = kWaves * vt.v[v].tiles_x * vt.v[v].tiles_y;
+    const int64_t p0 = (int64_t)kTileParts * vt.v[v].tile_off;
+    const int np = kTileParts * vt.v[v].tiles_x * vt.v[v].tiles_y;
     double x = 0.0;
     for (int i = threadIdx.x; i < np; i += blockDim.x) x += (double)loss_part[p0 + i];
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
@@ -1663,11 +1819,12 @@ __global__ __launch_bounds__(kBlock) void k_face_stats(ViewTable vt, const float
   __shared__ uint32_t sface[kWaves][kSlots];
   const int wv = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
-  const int tile = tile_of_block_ordered(vt.n_tiles, order);
-  if (tile < 0) return;
+  const Item it = item_of_block<true>(vt, order, ranges);
+  if (it.tile < 0) return;
   clear_empty_slots(1, srec[wv], nullptr, lane, kWave);
   TileCtx c;
-  tile_ctx(vt, ranges, tile, wv, c);
+  tile_ctx(vt, ranges, it, wv, c);
+  const bool upper = lane >= kWave / 2;
   float T = c.inside ? 1.f : 0.f, best_w = 0.f;
   int best = -1;
   const float dxb = (float)c.px, dyb = (float)c.py;
@@ -1675,48 +1832,71 @@ __global__ __launch_bounds__(kBlock) void k_face_stats(ViewTable vt, const float
     if (ballot(live(T, t_min)) == 0) break;
     const int n = (int)min((uint32_t)kBatch, c.end - b0);
     stage_span<SM, false>(records, pairs, b0, n, srec[wv], sface[wv], nullptr, 0, nullptr);
-    unsigned long long mask = batch_hit_mask<SM>(srec[wv], n, c.bx, c.by);
+    unsigned long long mask = batch_hit_mask<SM>(srec[wv], n, c.bx, c.by, c.bw);
     if (mask == 0ull) continue;
     bool lv = live(T, t_min);
     unsigned long long seen = 0ull;
-    auto visit = [&](const Rec& rc, int j) {
-      PixelEval e;
-      const bool act = eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e) && lv;
-      const float a = act ? e.alpha : 0.f;
+    auto blend = [&](float alpha, int j) {
+      const float a = lv ? alpha : 0.f;
       const float w = a * T;
-      const bool top = act && w > best_w;
+      const bool top = w > best_w;
       best_w = top ? w : best_w;
       best = top ? (int)b0 + j : best;
       // visible faces of the batch, one bit each (the empty record is never blended)
-      seen |= ballot(act) != 0ull ? 1ull << (j & 63) : 0ull;
+      seen |= ballot(a > 0.f) != 0ull ? 1ull << (j & 63) : 0ull;
       T = T * (1.f - a);
       lv = live(T, t_min);
     };
-    // two faces per round, each record loaded a face ahead (as forward_walk)
+    auto alpha_of = [&](const Rec& rc) {
+      PixelEval e;
+      eval_face<SM>(rc, dxb - rc.f[kRecU0], dyb - rc.f[kRecV0], sigma, e);
+      return fmaxf(e.alpha, 0.f);
+    };
+    // two faces per round, each record loaded a face ahead; in a split tile one in each half of the
+    // wave (as forward_walk)
     int j0 = first_bit(mask), j1 = first_bit(mask);
-    Rec r0, r1;
-    load_rec(srec[wv], j0, r0);
-    load_rec(srec[wv], j1, r1);
-    for (;;) {
-      visit(r0, j0);
-      j0 = first_bit(mask);
-      __builtin_amdgcn_sched_barrier(0);
+    if (it.split) {
+      Rec rc;
+      load_rec(srec[wv], upper ? j1 : j0, rc);
+      for (;;) {
+        const int f0 = j0, f1 = j1;
+        const float al = alpha_of(rc);
+        const Halves A = swap_halves(al, al);
+        j0 = first_bit(mask);
+        j1 = first_bit(mask);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rec(srec[wv], upper ? j1 : j0, rc);
+        __builtin_amdgcn_sched_barrier(0);
+        blend(A.f0, f0);
+        blend(A.f1, f1);
+        const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
+        if (done) break;
+      }
+    } else {
+      Rec r0, r1;
       load_rec(srec[wv], j0, r0);
-      __builtin_amdgcn_sched_barrier(0);
-      visit(r1, j1);
-      j1 = first_bit(mask);
-      __builtin_amdgcn_sched_barrier(0);
       load_rec(srec[wv], j1, r1);
-      __builtin_amdgcn_sched_barrier(0);
-      const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
-      if (done) break;
+      for (;;) {
+        blend(alpha_of(r0), j0);
+        j0 = first_bit(mask);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rec(srec[wv], j0, r0);
+        __builtin_amdgcn_sched_barrier(0);
+        blend(alpha_of(r1), j1);
+        j1 = first_bit(mask);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rec(srec[wv], j1, r1);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
+        if (done) break;
+      }
     }
     if (visible && ((seen >> lane) & 1ull)) visible[sface[wv][lane]] = 1u;
   }
   if (coverage) {
     // one atomic per distinct dominant face of the wave, adding its number of pixels (a large
     // face dominates many pixels, and atomics on one address serialise)
-    bool pending = best >= 0;
+    bool pending = best >= 0 && c.own;
     if (pending) best = (int)(uint32_t)pairs[best];          // list position -> face id
     for (;;) {
       const unsigned long long pm = ballot(pending);
@@ -1742,7 +1922,7 @@ hipError_t launch_face_stats(const ViewTable& vt, const tsr_params& p, const WsL
     if (coverage) TSR_LAUNCH("fill_stats", k_fill_f32, dim3(fg), dim3(256), 0, st, reinterpret_cast<float*>(coverage), nf);
     if (visible) TSR_LAUNCH("fill_stats", k_fill_f32, dim3(fg), dim3(256), 0, st, reinterpret_cast<float*>(visible), nf);
   }
-  const dim3 grid(tile_grid(vt.n_tiles)), block(kBlock);
+  const dim3 grid(vt.n_tiles + split_items(vt)), block(kBlock);
 #define TSR_STATS(S) TSR_LAUNCH("face_stats", k_face_stats<S>, grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, coverage, visible, border)
   TSR_MODE_SWITCH(sigma_mode(vt, p), TSR_STATS)
 #undef TSR_STATS
@@ -1757,7 +1937,7 @@ hipError_t launch_forward(const ViewTable& vt, const tsr_params& p, const WsLayo
   const int* border = tile_order(vt, L, ws, st);     // longest lists first
   int* n_last = reinterpret_cast<int*>(ws + L.n_last);
   float* t_last = reinterpret_cast<float*>(ws + L.t_last);
-  const dim3 grid(tile_grid(vt.n_tiles)), block(kBlock);
+  const dim3 grid(vt.n_tiles + split_items(vt)), block(kBlock);
   NormalIn nin{};
   if (nc)
     nin = NormalIn{reinterpret_cast<const float4*>(nc->face_normal), nullptr, nc->map, nc->poses, nc->target,
@@ -1813,7 +1993,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
   const dim3 block(kBlock);
   const int sm = sigma_mode(vt, p);
   if (!fused_train) {
-    const dim3 grid(tile_grid(vt.n_tiles));
+    const dim3 grid(vt.n_tiles + split_items(vt));
     const int* border = order;
     NormalIn nin{};
     if (nc)
@@ -1834,7 +2014,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
 #undef TSR_BWD
   } else {
     dim3 grid(tile_grid(vt.n_tiles));
-    if (sched.order && !sched.persistent) grid = dim3(vt.n_tiles);
+    if (sched.order && !sched.persistent) grid = dim3(vt.n_tiles + split_items(vt));
     if (sched.persistent) grid = dim3(sched.grid > 0 ? sched.grid : 2048);
     SeedScale scale;
     for (int v = 0; v < vt.n_views; ++v) {
@@ -1843,7 +2023,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
       scale.d[v] = p.w_depth / hw;
     }
     for (int v = vt.n_views; v < TSR_MAX_VIEWS; ++v) scale.c[v] = scale.d[v] = 0.f;
-#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", k_train_fused<S>, grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
+#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", (split_items(vt) > 0 ? k_train_fused<S, true> : k_train_fused<S, false>), grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
     TSR_MODE_SWITCH(sm, TSR_TRAIN)
 #undef TSR_TRAIN
   }

@@ -31,7 +31,7 @@ struct WsLayout {
   size_t hdr_sticky;               // uint32: some binning since the last tsr_check overflowed
   size_t pose_acc;                 // double [kSumCopies][V][6]
   size_t loss_acc;                 // double [kSumCopies][V]
-  size_t loss_part;                // float [T][4]: L1 loss of each (tile, 8x8 quadrant)
+  size_t loss_part;                // float [T][8]: L1 loss of each (tile, 8x8 quadrant, half)
   size_t counts;                   // uint32 [V*M]
   size_t records;                  // float  [V*M][24]
   size_t grad_acc;                 // float  [V*M][20]
@@ -77,7 +77,7 @@ constexpr int kWaveSortMax = 512;      // ... by one wave (longer ones by a whol
 constexpr int kSmallTiles = 4;         // faces overlapping at most this many tiles record their slots
 constexpr int kTileCntStride = 4;     // dwords per tile in the tile-counter array
 constexpr uint32_t kSkipSlot = 0xffffffffu;   // recorded slot of a tile the tight binning leaves out
-constexpr int kTileQuads = 4;          // 8x8 quadrants of a 16x16 tile (one blend wave each)
+constexpr int kTileParts = 8;          // partial sums of a 16x16 tile: two per 8x8 quadrant (one blend wave each)
 constexpr int kNormalPart = 8;         // floats of normal-loss sums per blend wave (mapping step)
 
 // What the emission of one visible (view, face) pair needs, written by the projection in the

@@ -370,7 +370,7 @@ MappingScratch mapping_scratch(size_t ssim_bytes, int64_t n_faces, int64_t n_til
   z.nrm = up(ssim_bytes);
   z.gacc = up(z.nrm + 16 * (size_t)n_faces);
   z.part = up(z.gacc + 16 * (size_t)n_faces);
-  z.count = up(z.part + sizeof(float) * kNormalPart * kTileQuads * (size_t)n_tiles);
+  z.count = up(z.part + sizeof(float) * kNormalPart * kTileParts * (size_t)n_tiles);
   z.acc = up(z.count + sizeof(uint32_t) * TSR_MAX_VIEWS);
   z.total = up(z.acc + sizeof(double) * 4 * TSR_MAX_VIEWS);
   return z;
@@ -385,8 +385,8 @@ __global__ __launch_bounds__(256) void k_normal_reduce(ViewTable vt, const float
   __shared__ double red[4];
   const int v = blockIdx.x;
   const ViewDesc vd = vt.v[v];
-  const int64_t w0 = (int64_t)vd.tile_off * kTileQuads;
-  const int64_t w1 = w0 + (int64_t)vd.tiles_x * vd.tiles_y * kTileQuads;
+  const int64_t w0 = (int64_t)vd.tile_off * kTileParts;
+  const int64_t w1 = w0 + (int64_t)vd.tiles_x * vd.tiles_y * kTileParts;
   double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   static_assert(kNormalPart == 8, "a slot is two float4");
   for (int64_t base = w0; base < w1; base += 4 * 256) {

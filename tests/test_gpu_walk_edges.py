@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle import oracle as O
+from paper_2605_31419_amd import raster
 from paper_2605_31419_amd import scenes as S
 from tests import gpu_util as G
 from tests import test_gpu_parity as PAR
@@ -75,3 +76,97 @@ def test_walks_at_batch_edges(n, opaque):
             for nm, a, b in zip(NAMES, out, sep):
                 a, b = a.cpu().numpy().astype(np.float64), b.cpu().numpy().astype(np.float64)
                 assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), (sched, nm)
+
+
+# 13 x 11 tiles, the faces of _tile around the middle one
+WIDE = S.Intrinsics(203, 171, 20.0, 20.0, 103.5, 87.5)
+PIX = 203 * 171
+
+
+def _same(a, b, scale=1.0):
+    a, b = a.detach().cpu().numpy().astype(np.float64), b.detach().cpu().numpy().astype(np.float64)
+    return np.linalg.norm(scale * a - b) <= 1e-5 * np.linalg.norm(b)
+
+
+def _longest(rast):
+    ranges = G.binning_arrays(rast)[2]
+    return int((ranges[:, 1] - ranges[:, 0]).max())
+
+
+@pytest.mark.parametrize("n", [150, 200, 333])
+@pytest.mark.parametrize("mode", [dict(sigma=1.0), dict(sigma=0.5), dict(sigma=2.0), dict(sigma=0.8), dict(face_sigma=True),
+                                  dict(sigma=1.0, perspective=True), dict(sigma=0.8, perspective=True)], ids=str)
+def test_split_tiles(mode, n):
+    """A tile of more than 128 faces is walked in two halves by two workgroups where it is in a single
+    view of at least 128 tiles, and whole where there are several views: the same view given once and
+    twice.  Images and
+    statistics are equal bit for bit, two equal views have twice the gradients, up to the order of
+    the FP32 sums."""
+    print(f"[split] mode={mode} n={n}", flush=True)
+    sc = _tile(n, n == 200)
+    mode = dict(mode)
+    if mode.pop("face_sigma", False):
+        sc = S.Scene(sc.pos, sc.col, sc.opa, None, np.linspace(0.4, 2.2, n).astype(np.float32))
+    dev = raster.DeviceScene.from_numpy(sc)
+    g = np.random.default_rng(n)
+    seeds = [g.normal(size=k * PIX).astype(np.float32) for k in (3, 1, 1)]
+    res = []
+    for views in (1, 2):
+        rast = raster.Rasterizer(dev, [WIDE] * views, raster.Params(**mode))
+        p = raster.poses_tensor([SHIFTED] * views)
+        rast.fit(p)
+        rast.bin_and_sort(p)
+        assert _longest(rast) > 128
+        img = [x.clone() for x in rast.forward(p)]
+        grads = [x.clone() for x in rast.backward(p, *[G.to_dev(np.tile(x, views)) for x in seeds])]
+        stats = [x.clone() for x in rast.face_stats(p)]
+        loss = torch.zeros(views, device="cuda")
+        tc, td = G.to_dev(np.tile(np.abs(seeds[0]) % 1, views)), G.to_dev(np.tile(1 + np.abs(seeds[1]), views))
+        fused = [[x.clone() for x in rast.train_l1(p, tc, td, loss=loss, schedule=s)] + [loss.clone()]
+                 for s in ((0, 1, 0), (1, 1, 64))]
+        res.append((img, grads, stats, fused))
+    torch.cuda.synchronize()
+    (img1, grads1, stats1, fused1), (img2, grads2, stats2, fused2) = res
+    for a, b in zip(img1, img2):
+        assert torch.equal(a, b[:a.numel()]) and torch.equal(a, b[a.numel():])
+    for a, b in zip(stats1, stats2):
+        assert torch.equal(a.reshape(-1), b.reshape(-1)[:a.numel()])
+    for one, two in [(grads1, grads2)] + [(x[:4], y[:4]) for x, y in zip(fused1, fused2)]:
+        for nm, a, b in zip(NAMES, one, two):
+            if nm == "grad_pose":
+                a = torch.cat([a.reshape(-1), a.reshape(-1)])
+                assert _same(a, b.reshape(-1)), nm
+            else:
+                assert _same(a, b, 2.0), nm
+    for x, y in zip(fused1, fused2):
+        assert _same(torch.cat([x[4], x[4]]), y[4])
+
+
+@pytest.mark.parametrize("n", [200, 333])
+def test_split_tiles_with_the_normal_channels(n):
+    """As test_split_tiles, the mapping step (colour, depth and normals in one walk)."""
+    from paper_2605_31419_amd.window import MappingWindow
+    print(f"[split] mapping step, n={n}", flush=True)
+    dev = raster.DeviceScene.from_numpy(_tile(n, False))
+    g = np.random.default_rng(n)
+    tc, td = g.uniform(0, 1, 3 * PIX).astype(np.float32), g.uniform(0.5, 4.0, PIX).astype(np.float32)
+    tn = g.normal(size=(3, PIX)).astype(np.float32)
+    tn = (tn / np.linalg.norm(tn, axis=0)).reshape(-1)
+    res = []
+    for views in (1, 2):
+        win = MappingWindow(dev, [WIDE] * views, w_ssim=0.2, w_norm=0.05)
+        p = raster.poses_tensor([SHIFTED] * views)
+        win.prepare(p)
+        grads = win.step(p, G.to_dev(np.tile(tc, views)), G.to_dev(np.tile(td, views)),
+                         target_normals=G.to_dev(np.tile(tn, views)))
+        torch.cuda.synchronize()
+        res.append([x.clone() for x in grads] + [win.loss.clone(), win.norm_loss.clone()])
+    one, two = res
+    for nm, a, b in zip(NAMES, one[:4], two[:4]):
+        if nm == "grad_pose":
+            a = torch.cat([a.reshape(-1), a.reshape(-1)])
+            assert _same(a, b.reshape(-1)), nm
+        else:
+            assert _same(a, b, 2.0), nm
+    for a, b in zip(one[4:], two[4:]):
+        assert _same(torch.cat([a.reshape(-1), a.reshape(-1)]), b.reshape(-1))

@@ -69,13 +69,15 @@ __global__ __launch_bounds__(256) void k_sensor_normals(const float* __restrict_
   const int64_t P = (int64_t)vd.width * vd.height;
   const float* d = depth + vd.pix_off;
   float* out = normals + 3 * vd.pix_off;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P; i += (int64_t)gridDim.x * blockDim.x) {
-    const int u = (int)(i % vd.width), y = (int)(i / vd.width);
+  // at most 2^28 pixels a view: 32-bit indices (a 64-bit division is some hundred instructions)
+  const uint32_t W = (uint32_t)vd.width;
+  const double ifx = 1.0 / (double)vd.fx, ify = 1.0 / (double)vd.fy;
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < (uint32_t)P; i += gridDim.x * blockDim.x) {
+    const int y = (int)(i / W), u = (int)(i - (uint32_t)y * W);
     double n[3] = {0.0, 0.0, 0.0};
     if (u >= 1 && u <= vd.width - 2 && y >= 1 && y <= vd.height - 2) {
-      const double dc = d[i], dl = d[i - 1], dr = d[i + 1], du = d[i - vd.width], dd = d[i + vd.width];
+      const double dc = d[i], dl = d[i - 1], dr = d[i + 1], du = d[i - W], dd = d[i + W];
       if (dc > 0.0 && dl > 0.0 && dr > 0.0 && du > 0.0 && dd > 0.0) {
-        const double ifx = 1.0 / (double)vd.fx, ify = 1.0 / (double)vd.fy;
         auto pt = [&](double z, int uu, int vv, double p[3]) {
           p[0] = z * ((double)uu - (double)vd.cx) * ifx;
           p[1] = z * ((double)vv - (double)vd.cy) * ify;
@@ -91,9 +93,11 @@ __global__ __launch_bounds__(256) void k_sensor_normals(const float* __restrict_
           gy[a] = 0.5 * (pd[a] - pu[a]);
         }
         cross3(gx, gy, c);
-        const double L = sqrt(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]);
-        if (L > 0.0)
-          for (int a = 0; a < 3; ++a) n[a] = c[a] / L;
+        const double L2 = c[0] * c[0] + c[1] * c[1] + c[2] * c[2];
+        if (L2 > 0.0) {
+          const double il = rsqrt(L2);
+          for (int a = 0; a < 3; ++a) n[a] = c[a] * il;
+        }
       }
     }
     for (int a = 0; a < 3; ++a) out[a * P + i] = (float)n[a];

@@ -45,8 +45,15 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None) -> C.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    # the handle alone: building a torch Stream object costs more than the rest of a call's arguments
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def intrinsics_array(intrs: Sequence) -> C.Array:

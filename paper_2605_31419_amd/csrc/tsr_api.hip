@@ -497,9 +497,9 @@ int tsr_face_stats(const tsr_scene* scene, const float* poses, const tsr_intrins
   if (!area && !coverage && !visible) return fail(TSR_EINVAL, "area, coverage and visible are all NULL");
   const hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
-  if (area) e = tsr::launch_face_area(dev_scene(scene, params), poses, vt, *params, area, st);
+  if (area) e = tsr::launch_face_area(dev_scene(scene, params), poses, vt, *params, area, coverage, visible, st);
   if (e == hipSuccess && (coverage || visible))
-    e = tsr::launch_face_stats(vt, *params, L, static_cast<char*>(ws), coverage, visible, st);
+    e = tsr::launch_face_stats(vt, *params, L, static_cast<char*>(ws), coverage, visible, area != nullptr, st);
   return e == hipSuccess ? TSR_OK : hip_fail(e, "tsr_face_stats launch");
 }
 

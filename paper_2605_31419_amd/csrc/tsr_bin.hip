@@ -1154,12 +1154,17 @@ hipError_t launch_ws_init(char* ws, hipStream_t st) {
 
 // Projected image-space area (pixels^2, half the absolute cross product of the projected
 // edges) of every (view, face) that survives the near-plane and inradius culls and overlaps the
-// image, 0 for the others; the same FP64 setup as the projection.  Thread idx = v * M + m.
+// image, 0 for the others; the same FP64 setup as the projection.  Thread idx = v * M + m.  Also clears
+// the counters of the walk that follows, where it is given them (two launches of their own before: 5 us
+// each for 1M faces).
 __global__ __launch_bounds__(256) void k_face_area(tsr_scene_dev sc, const float* __restrict__ poses, ViewTable vt,
-                                                   float z_near, float r_min, float* __restrict__ area) {
+                                                   float z_near, float r_min, float* __restrict__ area,
+                                                   uint32_t* __restrict__ coverage, uint32_t* __restrict__ visible) {
   const int64_t M = vt.n_faces;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)vt.n_views * M) return;
+  if (coverage) coverage[idx] = 0u;
+  if (visible) visible[idx] = 0u;
   const int v = (int)(idx / M);
   const int64_t m = idx - (int64_t)v * M;
   double R[9], t[3];
@@ -1172,11 +1177,11 @@ __global__ __launch_bounds__(256) void k_face_area(tsr_scene_dev sc, const float
 }
 
 hipError_t launch_face_area(const tsr_scene_dev& sc, const float* poses, const ViewTable& vt, const tsr_params& p,
-                            float* area, hipStream_t st) {
+                            float* area, uint32_t* coverage, uint32_t* visible, hipStream_t st) {
   const int64_t n = (int64_t)vt.n_views * vt.n_faces;
   if (n > 0)
     TSR_LAUNCH("face_area", k_face_area, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc, poses, vt,
-               p.z_near, p.r_min, area);
+               p.z_near, p.r_min, area, coverage, visible);
   return hipGetLastError();
 }
 

@@ -1610,8 +1610,16 @@ static const int* tile_order(const ViewTable& vt, const WsLayout& L, char* ws, h
   return order;
 }
 
-__global__ void k_fill_f32(float* __restrict__ p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0.f;
+// Zeroes up to three arrays in one launch (null: none; a launch costs more than the stores of a small one).
+__global__ __launch_bounds__(256) void k_zero3(uint32_t* __restrict__ a, int64_t na, uint32_t* __restrict__ b,
+                                               int64_t nb, uint32_t* __restrict__ c, int64_t nc) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (a)
+    for (int64_t i = i0; i < na; i += step) a[i] = 0u;
+  if (b)
+    for (int64_t i = i0; i < nb; i += step) b[i] = 0u;
+  if (c)
+    for (int64_t i = i0; i < nc; i += step) c[i] = 0u;
 }
 
 // Float outputs of the pose and loss sums.  `loss_part` is given when the face backward did
@@ -1911,17 +1919,15 @@ __global__ __launch_bounds__(kBlock) void k_face_stats(ViewTable vt, const float
 }
 
 hipError_t launch_face_stats(const ViewTable& vt, const tsr_params& p, const WsLayout& L, char* ws,
-                             uint32_t* coverage, uint32_t* visible, hipStream_t st) {
+                             uint32_t* coverage, uint32_t* visible, bool cleared, hipStream_t st) {
   const float* records = reinterpret_cast<const float*>(ws + L.records);
   const uint64_t* pairs = reinterpret_cast<const uint64_t*>(ws + L.pairs);
   const uint32_t* ranges = reinterpret_cast<const uint32_t*>(ws + L.ranges);
   const int* border = tile_order(vt, L, ws, st);     // longest lists first
   const int64_t nf = (int64_t)vt.n_views * vt.n_faces;
-  const unsigned fg = (unsigned)std::min<int64_t>((nf + 255) / 256, 4096);
-  if (nf > 0) {
-    if (coverage) TSR_LAUNCH("fill_stats", k_fill_f32, dim3(fg), dim3(256), 0, st, reinterpret_cast<float*>(coverage), nf);
-    if (visible) TSR_LAUNCH("fill_stats", k_fill_f32, dim3(fg), dim3(256), 0, st, reinterpret_cast<float*>(visible), nf);
-  }
+  if (nf > 0 && !cleared)
+    TSR_LAUNCH("fill_stats", k_zero3, dim3((unsigned)std::min<int64_t>((nf + 255) / 256, 4096)), dim3(256), 0, st, coverage,
+               nf, visible, nf, (uint32_t*)nullptr, (int64_t)0);
   const dim3 grid(vt.n_tiles + split_items(vt)), block(kBlock);
 #define TSR_STATS(S) TSR_LAUNCH("face_stats", k_face_stats<S>, grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, coverage, visible, border)
   TSR_MODE_SWITCH(sigma_mode(vt, p), TSR_STATS)
@@ -2032,11 +2038,12 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
   const bool want_vertices = grad_pos || grad_col || grad_opa;
   const bool want_gather = want_vertices || sc.grad_face_sigma;
   const int64_t N = sc.n_vertices;
-  if (sc.faces && want_vertices) {
-    if (grad_pos) TSR_LAUNCH("zero_grads", k_fill_f32, dim3(2048), dim3(256), 0, st, grad_pos, 3 * N);
-    if (grad_col) TSR_LAUNCH("zero_grads", k_fill_f32, dim3(2048), dim3(256), 0, st, grad_col, 3 * N);
-    if (grad_opa) TSR_LAUNCH("zero_grads", k_fill_f32, dim3(2048), dim3(256), 0, st, grad_opa, N);
-  }
+  auto zero_grads = [&] {
+    const unsigned g = (unsigned)std::min<int64_t>(std::max<int64_t>((3 * N + 255) / 256, 1), 2048);
+    TSR_LAUNCH("zero_grads", k_zero3, dim3(g), dim3(256), 0, st, reinterpret_cast<uint32_t*>(grad_pos), 3 * N,
+               reinterpret_cast<uint32_t*>(grad_col), 3 * N, reinterpret_cast<uint32_t*>(grad_opa), N);
+  };
+  if (sc.faces && want_vertices) zero_grads();
   if (nf > 0) {
     const dim3 fgrid(std::min<unsigned>(grid_for(nf, 256), 2048u));
     TSR_LAUNCH("face_bwd", k_face_bwd, fgrid, dim3(256), 0, st, sc, poses, vt, vis_total, vis_dense, records,
@@ -2049,9 +2056,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
       TSR_LAUNCH("zero_grads", k_zero_soup_tail, dim3(std::min<unsigned>(grid_for(N - 3 * vt.n_faces, 256), 1024u)),
                  dim3(256), 0, st, grad_pos, grad_col, grad_opa, N, 3 * vt.n_faces);
   } else if (want_vertices && !sc.faces) {
-    if (grad_pos) TSR_LAUNCH("zero_grads", k_fill_f32, dim3(2048), dim3(256), 0, st, grad_pos, 3 * N);
-    if (grad_col) TSR_LAUNCH("zero_grads", k_fill_f32, dim3(2048), dim3(256), 0, st, grad_col, 3 * N);
-    if (grad_opa) TSR_LAUNCH("zero_grads", k_fill_f32, dim3(2048), dim3(256), 0, st, grad_opa, N);
+    zero_grads();
   }
   if ((nf <= 0 || !want_gather) && (grad_pose || loss))     // otherwise k_vertex_gather converts them
     TSR_LAUNCH("finalize", k_finalize, dim3(1), dim3(kBlock), 0, st, vt, pose_acc, grad_pose, loss_acc,

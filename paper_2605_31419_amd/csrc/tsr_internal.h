@@ -239,9 +239,9 @@ hipError_t launch_equi(const tsr_scene_dev& sc, float weight, bool accumulate, f
 
 // Per-face screen statistics (pruning, densification and keyframing tests of Sec. 3.4).
 hipError_t launch_face_area(const tsr_scene_dev& sc, const float* poses, const ViewTable& vt, const tsr_params& p,
-                            float* area, hipStream_t st);
+                            float* area, uint32_t* coverage, uint32_t* visible, hipStream_t st);
 hipError_t launch_face_stats(const ViewTable& vt, const tsr_params& p, const WsLayout& L, char* ws,
-                             uint32_t* coverage, uint32_t* visible, hipStream_t st);
+                             uint32_t* coverage, uint32_t* visible, bool cleared, hipStream_t st);
 
 // Normal supervision (Sec. 3.4): scratch layout of the normal-loss step (byte offsets).
 struct NormalScratch {

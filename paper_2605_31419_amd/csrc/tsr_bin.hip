@@ -699,6 +699,84 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(uint32_t* __restrict__ tile
   }
 }
 
+// The same two scans for tables of more than one round, in two launches over chunks of 1024 entries, a
+// thread an entry: k_scan_sums the chunks' sums, k_scan_chunks each chunk from the sum of the chunks
+// before it.  A single workgroup takes 9 us a round (its loads, two barriers a round and the scan are
+// one chain): the 25,800 tiles and 15,600 segments of an 8-view 1200x680 window took 29 us, 10 (5 + 5)
+// now; one round, a view of 1200x680, is faster in the one launch (8 us).
+constexpr int kScanChunk = 1024;
+
+static inline int scan_chunks(int n) { return (n + kScanChunk - 1) / kScanChunk; }
+
+__global__ __launch_bounds__(kScanChunk) void k_scan_sums(const uint32_t* __restrict__ tile_cnt, int n_tiles,
+                                                          const uint32_t* __restrict__ vis_cnt, int n_segments,
+                                                          unsigned long long* __restrict__ tile_sum,
+                                                          unsigned long long* __restrict__ seg_sum, int tile_chunks) {
+  __shared__ unsigned long long wsum[16];
+  const bool tiles = (int)blockIdx.x < tile_chunks;
+  const int ch = tiles ? (int)blockIdx.x : (int)blockIdx.x - tile_chunks;
+  const int i = ch * kScanChunk + (int)threadIdx.x;
+  unsigned long long c = 0, tot;
+  if (tiles) {
+    if (i < n_tiles) c = (unsigned long long)tile_cnt[kTileCntStride * i] + tile_cnt[kTileCntStride * i + 2];
+  } else if (i < n_segments) {
+    c = vis_cnt[i];
+  }
+  block_excl_scan_u64(c, wsum, &tot);
+  if (threadIdx.x == 0) (tiles ? tile_sum : seg_sum)[ch] = tot;
+}
+
+__global__ __launch_bounds__(kScanChunk) void k_scan_chunks(
+    uint32_t* __restrict__ tile_cnt, uint32_t* __restrict__ ranges, int n_tiles, int64_t capacity,
+    int64_t* __restrict__ K_out, uint32_t* __restrict__ overflow, const uint32_t* __restrict__ vis_cnt,
+    uint32_t* __restrict__ vis_off, uint32_t* __restrict__ vis_total, int n_segments, uint32_t* __restrict__ long_cnt,
+    uint32_t* __restrict__ long_list, const unsigned long long* __restrict__ tile_sum,
+    const unsigned long long* __restrict__ seg_sum, int tile_chunks, int seg_chunks) {
+  __shared__ unsigned long long wsum[16];
+  const bool tiles = (int)blockIdx.x < tile_chunks;
+  const int ch = tiles ? (int)blockIdx.x : (int)blockIdx.x - tile_chunks;
+  const int nch = tiles ? tile_chunks : seg_chunks;
+  const unsigned long long* sums = tiles ? tile_sum : seg_sum;
+  const int i = ch * kScanChunk + (int)threadIdx.x;
+  uint32_t cs = 0, cb = 0;             // small-face and larger-face count of a tile, or a segment's count
+  if (tiles) {
+    if (i < n_tiles) {
+      cs = tile_cnt[kTileCntStride * i];
+      cb = tile_cnt[kTileCntStride * i + 2];
+    }
+  } else if (i < n_segments) {
+    cs = vis_cnt[i];
+  }
+  // sums of the chunks before this one and of all chunks
+  unsigned long long before = 0, all = 0, tot, carry;
+  for (int k = threadIdx.x; k < nch; k += kScanChunk) {
+    const unsigned long long x = sums[k];
+    all += x;
+    if (k < ch) before += x;
+  }
+  block_excl_scan_u64(before, wsum, &carry);
+  block_excl_scan_u64(all, wsum, &tot);
+  const unsigned long long total = tot;
+  const unsigned long long c = (unsigned long long)cs + cb;
+  const unsigned long long run = carry + block_excl_scan_u64(c, wsum, &tot);
+  if (!tiles) {
+    if (i < n_segments) vis_off[i] = (uint32_t)run;
+    if (ch == 0 && threadIdx.x == 0) *vis_total = (uint32_t)total;
+    return;
+  }
+  const bool over = total > (unsigned long long)capacity;
+  if (i < n_tiles) {
+    reinterpret_cast<uint2*>(ranges)[i] = over ? make_uint2(0u, 0u) : make_uint2((uint32_t)run, (uint32_t)(run + c));
+    tile_cnt[kTileCntStride * i + 2] = cs;       // base of the larger faces' cursor
+    if (c > (unsigned long long)kWaveSortMax) long_list[atomicAdd(long_cnt, 1u)] = (uint32_t)i;
+  }
+  if (ch == 0 && threadIdx.x == 0) {
+    *K_out = (int64_t)total;
+    overflow[0] = over ? 1u : 0u;     // this binning
+    if (over) overflow[2] = 1u;       // sticky until tsr_check reads it (spans graph replays)
+  }
+}
+
 // Emission of (float32 z_F bits << 32 | face) into each overlapped tile's bucket.  One
 // workgroup per visible-list segment, one lane per visible face of the segment (compacted,
 // in pair order), each reading its 32-byte visible-list entry.  Small faces store at their
@@ -1222,9 +1300,23 @@ hipError_t launch_bin(const tsr_scene_dev& sc, const float* poses, const ViewTab
   uint32_t* vis_total = reinterpret_cast<uint32_t*>(ws + L.vis_total);
   uint32_t* vis_dense = reinterpret_cast<uint32_t*>(ws + L.vis_dense);
   const int n_seg = (int)proj_segments(nf, vt.n_views);
-  TSR_LAUNCH("scan_tiles", k_scan_tiles, dim3(2), dim3(1024), 0, st, tile_cnt, ranges, vt.n_tiles,
-                     sort ? L.capacity : (int64_t)0x7fffffffffffffffll, K, overflow, vis_cnt, vis_off, vis_total,
-                     n_seg, long_cnt, long_list);
+  const int64_t scan_cap = sort ? L.capacity : (int64_t)0x7fffffffffffffffll;
+  if (vt.n_tiles <= kScanRound && n_seg <= kScanRound) {
+    TSR_LAUNCH("scan_tiles", k_scan_tiles, dim3(2), dim3(1024), 0, st, tile_cnt, ranges, vt.n_tiles, scan_cap, K, overflow,
+               vis_cnt, vis_off, vis_total, n_seg, long_cnt, long_list);
+  } else {
+    // the chunks' sums lie where later launches write: the tile order (4 bytes a tile, written beside the
+    // sorts) and the dense visible list (4 bytes a pair, written by the emission); both are 256-byte
+    // aligned parts, so there is room for a table of one chunk too
+    unsigned long long* tile_sum = reinterpret_cast<unsigned long long*>(ws + L.order);
+    unsigned long long* seg_sum = reinterpret_cast<unsigned long long*>(vis_dense);
+    const int tc = scan_chunks(vt.n_tiles), sch = scan_chunks(n_seg);
+    TSR_LAUNCH("scan_sums", k_scan_sums, dim3(tc + sch), dim3(kScanChunk), 0, st, tile_cnt, vt.n_tiles, vis_cnt, n_seg,
+               tile_sum, seg_sum, tc);
+    // (without segments nothing else writes their total)
+    TSR_LAUNCH("scan_tiles", k_scan_chunks, dim3(tc + std::max(sch, 1)), dim3(kScanChunk), 0, st, tile_cnt, ranges, vt.n_tiles,
+               scan_cap, K, overflow, vis_cnt, vis_off, vis_total, n_seg, long_cnt, long_list, tile_sum, seg_sum, tc, sch);
+  }
   if (!sort) return hipGetLastError();
   if (nf > 0) {
     if (p.tight_tiles)

@@ -25,6 +25,8 @@
 // the hit masks, the seeds and the wave maximum.  The backward takes the masks that the forward
 // formed for the span still in LDS, the seeds' scales come from the host, the maximum goes by
 // DPP: window 629 -> 616 us, 640x480 tracking 542 -> 533 us for eight iterations.
+//   These are whole tiles; the long ones of a single view are split (Item), after which that view's
+// fused launch is bound by its VALU instructions too (594 faces: 116 us of 122).
 #include "tsr_internal.h"
 
 namespace tsr {
@@ -892,9 +894,12 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
 
 // ---------------------------------------------------------------------------- kernels
 
-// The partial-sum slot of a wave: two per quadrant of a tile (an unsplit tile's wave fills both).
-__device__ __forceinline__ int64_t part_of(const Item& it, int quad) {
-  return 2 * ((int64_t)it.tile * kWaves + quad) + it.half;
+// The normal sums' slot of a wave: one per quadrant of a tile, two in a single view (an unsplit
+// tile's wave fills both).
+template <bool ONE>
+__device__ __forceinline__ int64_t normal_slot(const Item& it, int quad) {
+  const int64_t q = (int64_t)it.tile * kWaves + quad;
+  return ONE ? 2 * q + it.half : q;
 }
 
 // COOP (several views): the tile's list is staged cooperatively (one shared copy per workgroup, the four
@@ -955,10 +960,10 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const flo
     }
     const float tc = wave_sum(cnt), tl = wave_sum(l), t0 = wave_sum(r0), t1 = wave_sum(r1), t2 = wave_sum(r2);
     if ((threadIdx.x & 63) == 0) {
-      float4* pw = reinterpret_cast<float4*>(nin.part + kNormalPart * part_of(it, wv));
+      float4* pw = reinterpret_cast<float4*>(nin.part + kNormalPart * normal_slot<!COOP>(it, wv));
       pw[0] = make_float4(tc, tl, t0, t1);
       pw[1] = make_float4(t2, 0.f, 0.f, 0.f);
-      if (!it.split) pw[2] = pw[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (!COOP && !it.split) pw[2] = pw[3] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
   if (!c.own) return;
@@ -1049,7 +1054,7 @@ struct SeedScale {
 
 // Fused training kernel (ONE: of a single view that may have split tiles): forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
 // images and runs in tsr_ssim.hip between a separate forward and backward), backward
-// walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant).
+// walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant, half).
 // Five workgroups per CU (96 registers a lane): the records of two faces in flight.
 template <int SM, bool ONE>
 __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
@@ -1422,34 +1427,25 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
   }
 }
 
-// Float outputs of the FP64 pose and loss sums: one wave per sum adds its kSumCopies copies, one
-// per lane, so that the copies cost one memory round trip (a loop over them by one thread took
-// eight).
+// Float outputs of the FP64 pose and loss sums (adding their kSumCopies copies).
 __device__ __forceinline__ void write_sums(const ViewTable& vt, const double* __restrict__ pose_acc,
                                            float* __restrict__ grad_pose, const double* __restrict__ loss_acc,
                                            float* __restrict__ loss) {
-  static_assert(kSumCopies == kWave, "one copy per lane");
-  const int nv = vt.n_views, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-  constexpr int kU = 4;                      // sums per wave in flight
-  for (int k0 = threadIdx.x >> 6; k0 < 7 * nv; k0 += kU * nw) {
-    double t[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * nw;
-      const double* src = k < 6 * nv ? pose_acc + k : loss_acc + (k - 6 * nv);
-      t[u] = k < 7 * nv ? src[(int64_t)lane * (k < 6 * nv ? 6 * nv : nv)] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * nw;
-      for (int o = 32; o > 0; o >>= 1) t[u] += __shfl_xor(t[u], o, 64);
-      if (lane == 0 && k < 6 * nv && grad_pose) grad_pose[k] = (float)t[u];
-      if (lane == 0 && k >= 6 * nv && k < 7 * nv && loss) loss[k - 6 * nv] = (float)t[u];
-    }
+  const int nv = vt.n_views;
+  for (int k = threadIdx.x; k < 7 * nv; k += blockDim.x) {
+    const bool is_pose = k < 6 * nv;
+    if (is_pose ? !grad_pose : !loss) continue;
+    const double* src = is_pose ? pose_acc + k : loss_acc + (k - 6 * nv);
+    const int stride = is_pose ? 6 * nv : nv;
+    double t = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < kSumCopies; ++c) t += src[(int64_t)c * stride];
+    if (is_pose) grad_pose[k] = (float)t;
+    else loss[k - 6 * nv] = (float)t;
   }
 }
 
-// Per-view L1 loss: FP64 sum of the (tile, quadrant) parts of the view's tiles, by one
+// Per-view L1 loss: FP64 sum of the kTileParts parts of the view's tiles, by one
 // workgroup of kBlock threads (every thread calls).
 __device__ void reduce_view_losses(const ViewTable& vt, const float* __restrict__ loss_part, float* __restrict__ loss) {
   __shared__ double red[kWaves];
@@ -1623,7 +1619,7 @@ __global__ __launch_bounds__(256) void k_zero3(uint32_t* __restrict__ a, int64_t
 }
 
 // Float outputs of the pose and loss sums.  `loss_part` is given when the face backward did
-// not run (no faces): the per-view losses are then summed here from the (tile, quadrant) parts.
+// not run (no faces): the per-view losses are then summed here from the tiles' parts.
 __global__ __launch_bounds__(kBlock) void k_finalize(ViewTable vt, const double* __restrict__ pose_acc,
                                                      float* __restrict__ grad_pose, const double* __restrict__ loss_acc,
                                                      const float* __restrict__ loss_part, float* __restrict__ loss) {
@@ -1733,7 +1729,7 @@ __global__ void k_pose_compose(const float* __restrict__ tau, const float* __res
 // ad(rho, theta) = [[theta]x, [rho]x; 0, [theta]x] (translation first), so J_l^T g is summed by
 // its terms t_0 = g, t_n = ad^T t_(n-1) / (n+1): with t = (a, b), ad^T t = (a x theta, a x rho +
 // b x theta), four cross products' worth of FP64 per term instead of the 6x6 powers (45 us for
-// one view, 5 with the vectors: one lane runs it, so its length is its instructions).  Summed
+// one view, 2.4 with the vectors: one lane runs it, so its length is its instructions).  Summed
 // until, past the largest terms (n + 1 > 2 |ad|), a term falls below 1e-17 of the running sum, at
 // most 80 terms.
 __global__ void k_pose_tau_grad(const float* __restrict__ tau, const float* __restrict__ grad_pose, int n_views,

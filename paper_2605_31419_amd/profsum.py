@@ -86,7 +86,7 @@ def main():
     ap.add_argument("db", nargs="?")
     ap.add_argument("--fetch")
     ap.add_argument("--write")
-    ap.add_argument("--kernel", action="append", help="kernel name (repeatable); default k_train_fused<1>")
+    ap.add_argument("--kernel", action="append", help="kernel name (repeatable); default k_train_fused")
     a = ap.parse_args()
     if a.mode == "kernels":
         print_kernels(a.db)
@@ -96,7 +96,7 @@ def main():
         from .build import source_fingerprint
 
         fp = source_fingerprint()
-        for i, k in enumerate(a.kernel or ["k_train_fused<1>"]):
+        for i, k in enumerate(a.kernel or ["k_train_fused"]):
             t = traffic(a.fetch, a.write, k)
             if i == 0:
                 print(f"calibration: fetched bytes = {t['fetch_factor']:.3f} x FETCH_SIZE, "

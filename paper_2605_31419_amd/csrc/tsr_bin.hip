@@ -211,7 +211,7 @@ __device__ __forceinline__ void write_record(const FaceAttr& at, const FaceSetup
   rec[kRecZ] = (float)f.zf;
   rec[kRecU0] = (float)f.u0;          // exact: |u0| < 2^24
   rec[kRecV0] = (float)f.v0;
-  rec[kRecU1V1] = __int_as_float(f.u1 | (f.v1 << 16));    // both below 2^14
+  rec[kRecMid] = __int_as_float((f.u0 + f.u1) | ((f.v0 + f.v1) << 16));    // both below 2^15
   rec[kRecSigma] = at.sigma;
   if (at.persp) {
     // denominator plane W = sum_k lambda_opp(k) / z_opp(k) (1 / depth of the face's plane)

@@ -69,11 +69,18 @@ struct Item {
 // kernels are built without the split walks (their registers cost the 8-view window 2 %), and the few
 // workgroups of a small image gain nothing and wait for the larger kernel's instructions (64x48: the
 // step 45.4 -> 47.0 us).
+//   Every visit of a half adds its face's sums to memory on its own, so the faces of split tiles take up to
+// twice as many FP32 additions; the backwards that may split therefore take the planes' moments about
+// the middle of the face (backward_walk).  A perspective-correct record has no room for it: those
+// backwards walk whole tiles.
 // One 1200x680 view of 1M faces: forward 73 -> 55 us, backward 128 -> 117, fused 161 -> 139, face
 // statistics 61 -> 48.
 constexpr int kSplitMax = 256;           // split tiles at most: the first of the longest-first order
 constexpr uint32_t kSplitDiv = 1536, kSplitMin = 128;
 constexpr int kSplitTiles = 128;         // tiles of the view from which on tiles are split
+
+// Whether a backward in this mode may split tiles.
+template <int SM> constexpr bool split_bwd() { return (SM & 8) == 0; }
 
 static __host__ __device__ inline int split_items(const ViewTable& vt) {
   return vt.n_views == 1 && vt.n_tiles >= kSplitTiles ? min(kSplitMax, vt.n_tiles / 8) : 0;
@@ -387,8 +394,8 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
   }
   if (j < n) {
     const float4 rc = srec[kRecU0 / 4 * kSlots + j];
-    const int u1v1 = __float_as_int(rc.z);
-    const int u0 = (int)rc.x, v0 = (int)rc.y, u1 = u1v1 & 0xffff, v1 = u1v1 >> 16;
+    const int mid = __float_as_int(rc.z);
+    const int u0 = (int)rc.x, v0 = (int)rc.y, u1 = (mid & 0xffff) - u0, v1 = (mid >> 16) - v0;
     const int xl = max(bx, u0), xh = min(bx + bw - 1, u1), yl = max(by, v0), yh = min(by + 7, v1);
     hit = xl <= xh && yl <= yh;
     if (hit) {
@@ -592,9 +599,9 @@ struct PixGrad {
 };
 
 // One face's gradient terms at a pixel, as the wave sums take them: p0 the terms that also have
-// a moment with respect to dy (the three edges' dL/dE_k, the three colours' dL/dc_ch, then
+// a moment with respect to y (the three edges' dL/dE_k, the three colours' dL/dc_ch, then
 // dL/do_F without one, and the z_F term or, perspective-correct, the W plane's dL/dW with one),
-// p1 the moments with respect to dx (edges, colours, then the W plane's or the term of the face's
+// p1 the moments with respect to x (edges, colours, then the W plane's or the term of the face's
 // own exponent), p2 the normal channels.
 template <int SM> constexpr int p1_terms() { return persp_mode<SM>() || exp_mode<SM>() == 4 ? 7 : 6; }
 
@@ -604,12 +611,12 @@ struct FaceTerms {
 };
 
 // Sums of the two faces' terms, each over its half of the wave; lane l holds one total of its
-// half's face (which one: grad_lane).  p0 and p1 over the row of pixels first, then Q0 = P0 dy, then
+// half's face (which one: grad_lane).  p0 and p1 over the row of pixels first, then Q0 = P0 y, then
 // P0, P1, Q0 (and p2) over the rows.
 template <int SM>
-__device__ __forceinline__ float sum_face(FaceTerms<SM>& ft, float dy) {
+__device__ __forceinline__ float sum_face(FaceTerms<SM>& ft, float y) {
   sum_x(ft.p0, ft.p1);
-  float q0 = ft.p0[0] * dy, q1 = ft.p0[4] * dy, out;
+  float q0 = ft.p0[0] * y, q1 = ft.p0[4] * y, out;
   if constexpr (normal_mode<SM>()) {
     sum_x(ft.p2);
     out = sum_y(ft.p0[0], ft.p0[4], ft.p1[0], ft.p1[4], q0, q1, ft.p2[0]);
@@ -695,7 +702,11 @@ __device__ __forceinline__ void add_total(const GradLane& gl, uint32_t g, float 
 // S = gC.B + gD BD - gT BA, so S is carried instead: with P = gC.c + gD z - gT for the face,
 // dL/dalpha = T (P - S) and S <- alpha P + (1 - alpha) S.  Per-face sums of the 20
 // record-parameter gradients are reduced over the wave and added to grad_acc.
-template <int SM, bool COOP, bool SPLIT, int SPAN = kSpan>
+//   MID: the planes' moments are about the middle of the face's rectangle instead of its anchor
+// (GradField): five more instructions a round, which do not show in the times (1200x680 step of 1M
+// faces 243 us either way), and the colour gradients' error against 64 bits 1.0e-6 to 1.4e-6 -> 0.4e-6
+// to 0.5e-6 on a map with 161 split tiles, 5e-7 -> 2.8e-7 on one with 131.
+template <int SM, bool COOP, bool SPLIT, bool MID, int SPAN = kSpan>
 __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __restrict__ records,
                                               const uint64_t* __restrict__ pairs, float sigma, int last, float Tb,
                                               const PixGrad& pg, float4* srec, uint32_t* sface, int* sint,
@@ -786,6 +797,13 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
       const uint32_t id = sf[jl];
       const float dx = dxb - rc.f[kRecU0], dxB = dx + 4.f;
       const float dy = dyb - rc.f[kRecV0];
+      float mx = dx, mxB = dxB, my = dy;       // offsets that the moments are taken of
+      if constexpr (MID) {
+        const uint32_t mid = (uint32_t)__float_as_int(rc.f[kRecMid]);
+        mx = fmaf(-0.5f, (float)(mid & 0xffffu), dxb);
+        mxB = mx + 4.f;
+        my = fmaf(-0.5f, (float)(mid >> 16), dyb);
+      }
       PixelEval e[NP];
       bool act[NP];
       float alpha[NP], P[NP];
@@ -828,12 +846,12 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
       }
       Tcur = T1;
       S = fmaf(ca.f1, cp.f1, om1 * S1);
-      // Sums of the two pixels' terms and of their moments with respect to dx.
+      // Sums of the two pixels' terms and of their moments with respect to x.
       // colour plane gradients: dL/dc_ch(p) = gC_ch alpha T, and c_ch = P dx + Q dy + R
       FaceTerms<SM> ft;
       auto add = [&](int k, float ta, float tb) {
         ft.p0[k] = SPLIT ? ta : ta + tb;
-        if (k < 6) ft.p1[k] = SPLIT ? ta * dx : fmaf(tb, dxB, ta * dx);
+        if (k < 6) ft.p1[k] = SPLIT ? ta * mx : fmaf(tb, mxB, ta * mx);
       };
       float galpha[NP], gc[NP][3], gz[NP], gk[NP][3];
 #pragma unroll
@@ -882,8 +900,8 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
       for (int k = 0; k < 3; ++k) add(3 + k, gc[0][k], gc[NP - 1][k]);
       ft.p0[6] = SPLIT ? galpha[0] * e[0].I : fmaf(galpha[0], e[0].I, galpha[NP - 1] * e[NP - 1].I);
       add(7, gz[0], gz[NP - 1]);
-      if constexpr (persp_mode<SM>()) ft.p1[6] = SPLIT ? gz[0] * dx : fmaf(gz[NP - 1], dxB, gz[0] * dx);
-      const float tot = sum_face<SM>(ft, dy);
+      if constexpr (persp_mode<SM>()) ft.p1[6] = SPLIT ? gz[0] * mx : fmaf(gz[NP - 1], mxB, gz[0] * mx);
+      const float tot = sum_face<SM>(ft, my);
       // one atomic per lane that holds a total (0 for the empty record)
       if (gl.any) add_total<SM>(gl, id, tot);
       if (j0 == kBatch) break;
@@ -986,8 +1004,9 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const flo
                                                       const float* __restrict__ gtrans, acc_t* __restrict__ grad_acc,
                                                       float* __restrict__ sig_acc, float* __restrict__ persp_acc,
                                                       const int* __restrict__ order, NormalIn nin) {
+  constexpr bool ONE = !COOP && split_bwd<SM>();
   const int wv = threadIdx.x >> 6;
-  const Item it = item_of_block<!COOP>(vt, order, ranges);
+  const Item it = item_of_block<ONE>(vt, order, ranges);
   if (it.tile < 0) return;
   TileCtx c;
   tile_ctx(vt, ranges, it, wv, c);
@@ -1030,19 +1049,19 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_bwd(ViewTable vt, const flo
     __shared__ float4 snrm[normal_mode<SM>() ? span_batches(kSepSpan) * kSlots : 1];
     clear_empty_slots(span_batches(kSepSpan), srec, normal_mode<SM>() ? snrm : nullptr, threadIdx.x, kBlock);
     __shared__ int sint[4];
-    backward_walk<SM, true, false, kSepSpan>(c, records, pairs, sigma, last, Tb, pg, srec, sface, sint, grad_acc,
-                                             sig_acc, persp_acc, &nin, snrm);
+    backward_walk<SM, true, false, false, kSepSpan>(c, records, pairs, sigma, last, Tb, pg, srec, sface, sint, grad_acc,
+                                                    sig_acc, persp_acc, &nin, snrm);
   } else {
     __shared__ float4 srec[kWaves][kBatchVec];
     __shared__ uint32_t sface[kWaves][kSlots];
     __shared__ float4 snrm[kWaves][normal_mode<SM>() ? kSlots : 1];
     clear_empty_slots(1, srec[wv], normal_mode<SM>() ? snrm[wv] : nullptr, threadIdx.x & 63, kWave);
-    if (it.split)
-      backward_walk<SM, false, true>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc,
-                                     sig_acc, persp_acc, &nin, snrm[wv]);
+    if (ONE && it.split)
+      backward_walk<SM, false, ONE, ONE>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc,
+                                         sig_acc, persp_acc, &nin, snrm[wv]);
     else
-      backward_walk<SM, false, false>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr, grad_acc,
-                                      sig_acc, persp_acc, &nin, snrm[wv]);
+      backward_walk<SM, false, false, ONE>(c, records, pairs, sigma, last, Tb, pg, srec[wv], sface[wv], nullptr,
+                                           grad_acc, sig_acc, persp_acc, &nin, snrm[wv]);
   }
 }
 
@@ -1155,11 +1174,11 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       if (lane == 1 && !it.split) loss_part[part + 1] = 0.f;
     }
     if (ONE && it.split)
-      backward_walk<SM, true, ONE>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
-                                   persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
+      backward_walk<SM, true, ONE, ONE>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
+                                        persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
     else
-      backward_walk<SM, true, false>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
-                                     persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
+      backward_walk<SM, true, false, ONE>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc,
+                                          sig_acc, persp_acc, nullptr, nullptr, s.staged, s_hits[wv]);
     if (!persistent) break;
   }
 }
@@ -1186,7 +1205,7 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
                                                   const uint32_t* __restrict__ vis_total,
                                                   const uint32_t* __restrict__ vis_dense,
                                                   const float* __restrict__ records, acc_t* grad_acc,
-                                                  const float* __restrict__ persp_acc,
+                                                  const float* __restrict__ persp_acc, int mid,
                                                   double* __restrict__ pose_acc, int want_vertices,
                                                   const float* __restrict__ loss_part, double* __restrict__ loss_acc) {
   const bool persp = persp_acc != nullptr;        // perspective-correct records
@@ -1279,7 +1298,13 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
       n[k][0] = so * e[k][1] * inv_len[k];
       n[k][1] = -so * e[k][0] * inv_len[k];
     }
-    const double U0 = (double)rec[kRecU0], V0 = (double)rec[kRecV0];
+    // the point that the planes' moments are about: the record's anchor, or (mid) the rectangle's middle
+    double U0 = (double)rec[kRecU0], V0 = (double)rec[kRecV0];
+    if (mid) {
+      const int w = __float_as_int(rec[kRecMid]);
+      U0 = 0.5 * (double)(w & 0xffff);
+      V0 = 0.5 * (double)(w >> 16);
+    }
     double ca[3], cb[3], cc[3];       // edge coefficients a_k, b_k, c_k
     for (int k = 0; k < 3; ++k) {
       ca[k] = -n[k][0] * inv_r;
@@ -1994,14 +2019,18 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
   }
   const dim3 block(kBlock);
   const int sm = sigma_mode(vt, p);
+  const int n_items = vt.n_tiles + (p.perspective ? 0 : split_items(vt));
+  const bool coop = separate_coop(vt);
+  // which moments the walks take (as the kernels chosen below are built)
+  const bool one = split_items(vt) > 0;
+  const bool mid = !p.perspective && (fused_train ? one : !coop);
   if (!fused_train) {
-    const dim3 grid(vt.n_tiles + split_items(vt));
+    const dim3 grid(n_items);
     const int* border = order;
     NormalIn nin{};
     if (nc)
       nin = NormalIn{reinterpret_cast<const float4*>(nc->face_normal), reinterpret_cast<float4*>(nc->grad), nullptr,
                      nc->poses, nc->target, nc->count, nullptr, nc->w_norm, vt.n_faces};
-    const bool coop = separate_coop(vt);
 #define TSR_BWD(S)                                                                                 \
   {                                                                                                \
     auto kb = coop ? k_blend_bwd<S, true> : k_blend_bwd<S, false>;                                 \
@@ -2016,7 +2045,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
 #undef TSR_BWD
   } else {
     dim3 grid(tile_grid(vt.n_tiles));
-    if (sched.order && !sched.persistent) grid = dim3(vt.n_tiles + split_items(vt));
+    if (sched.order && !sched.persistent) grid = dim3(n_items);
     if (sched.persistent) grid = dim3(sched.grid > 0 ? sched.grid : 2048);
     SeedScale scale;
     for (int v = 0; v < vt.n_views; ++v) {
@@ -2025,7 +2054,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
       scale.d[v] = p.w_depth / hw;
     }
     for (int v = vt.n_views; v < TSR_MAX_VIEWS; ++v) scale.c[v] = scale.d[v] = 0.f;
-#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", (split_items(vt) > 0 ? k_train_fused<S, true> : k_train_fused<S, false>), grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
+#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", (one ? k_train_fused<S, split_bwd<S>()> : k_train_fused<S, false>), grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
     TSR_MODE_SWITCH(sm, TSR_TRAIN)
 #undef TSR_TRAIN
   }
@@ -2043,7 +2072,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
   if (nf > 0) {
     const dim3 fgrid(std::min<unsigned>(grid_for(nf, 256), 2048u));
     TSR_LAUNCH("face_bwd", k_face_bwd, fgrid, dim3(256), 0, st, sc, poses, vt, vis_total, vis_dense, records,
-               grad_acc, persp_acc, grad_pose ? pose_acc : nullptr, want_vertices ? 1 : 0, loss ? loss_part : nullptr,
+               grad_acc, persp_acc, mid ? 1 : 0, grad_pose ? pose_acc : nullptr, want_vertices ? 1 : 0, loss ? loss_part : nullptr,
                loss_acc);
     if (want_gather)
       TSR_LAUNCH("vertex_gather", k_vertex_gather, dim3(grid_for(vt.n_faces, 256)), dim3(256), 0, st, sc, vt, counts,

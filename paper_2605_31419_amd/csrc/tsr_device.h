@@ -27,7 +27,8 @@ enum RecordField : int {
   kRecZ = 19,        // z_F
   kRecU0 = 20,       // u0 as a float (an exact integer)
   kRecV0 = 21,       // v0 as a float (an exact integer)
-  kRecU1V1 = 22,     // int u1 | (v1 << 16)  (image sizes are at most 16384)
+  kRecMid = 22,      // int (u0 + u1) | (v0 + v1) << 16, (u1, v1) the rectangle's last pixel: twice its
+                     // middle (image sizes are at most 16384)
   kRecSigma = 23,    // the face's window exponent sigma (eq. 3)
   kRecDwords = 24
 };
@@ -35,11 +36,14 @@ enum RecordField : int {
 // perspective-correct colour, sum_k lambda_k c_k / z_k, and three dwords the plane of the
 // denominator W = sum_k lambda_k / z_k (W = 1 / depth of the face's plane along the ray); the
 // depth z_F, the rectangle's end and the per-face exponent are not stored.
-enum PerspField : int { kRecWa = kRecZ, kRecWb = kRecU1V1, kRecWc = kRecSigma };
+enum PerspField : int { kRecWa = kRecZ, kRecWb = kRecMid, kRecWc = kRecSigma };
 
 // Per-(view, face) gradient accumulator, 20 values, filled by the backward blend:
 // dL/d(a_k, b_k, c_k) for the three edges, dL/d(P, Q, R) per channel, dL/do_F, dL/dz_F.
 // Wave partial sums are FP32; they are accumulated across waves and tiles in acc_t.
+// The planes' moments are about the anchor (u0, v0) or, where tiles may be split between two workgroups
+// (and a face then takes up to twice as many additions), about the rectangle's middle: the chain rule
+// combines the three of a plane with cancellation, and about the middle they are half as large.
 enum GradField : int { kGEdge = 0, kGCol = 9, kGOpa = 18, kGZ = 19, kGradDwords = 20 };
 // Perspective-correct mode: the colour slots hold dL/d(N_ch plane), kGZ dL/d(constant of the W
 // plane); the W plane's two slopes go to a second per-(view, face) accumulator of 2 floats.

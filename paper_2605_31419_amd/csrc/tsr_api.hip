@@ -157,6 +157,9 @@ WsLayout layout(const ViewTable& vt, int64_t cap) {
   L.vis_cnt = o; o = align_up(o + sizeof(uint32_t) * nb);
   L.vis_off = o; o = align_up(o + sizeof(uint32_t) * nb);
   L.vis_total = o; o = align_up(o + sizeof(uint32_t));
+  L.scan_sums = o;
+  if (tsr::scan_in_chunks(vt.n_tiles, nb))
+    o = align_up(o + sizeof(uint64_t) * (tsr::scan_chunks(vt.n_tiles) + tsr::scan_chunks(nb)));
   L.vis_list = o; o = align_up(o + sizeof(tsr::VisEntry) * nb * tsr::kProjBlock);
   L.vis_dense = o; o = align_up(o + sizeof(uint32_t) * nf);
   L.ranges = o; o = align_up(o + sizeof(uint32_t) * 2 * vt.n_tiles);

@@ -564,10 +564,7 @@ __global__ __launch_bounds__(256, 4) void k_project(tsr_scene_dev sc, const floa
 // visible list); (1) exclusive scan of the tile counts into ranges, pair total K, overflow check against the capacity (all
 // ranges empty on overflow), the small-face counts left in tile_cnt2 as the base of the
 // larger faces' emission cursors, and the list of tiles too long for the one-wave sort.  Both
-// scans run in rounds of kScanRound entries, each thread taking kScanPer consecutive ones (10:
-// with 12 the 128 registers of a 1024-thread workgroup spill).
-constexpr int kScanPer = 10;
-constexpr int kScanRound = 1024 * kScanPer;
+// scans run in rounds of kScanRound entries, each thread taking kScanPer consecutive ones.
 
 __global__ __launch_bounds__(1024) void k_scan_tiles(uint32_t* __restrict__ tile_cnt, uint32_t* __restrict__ ranges,
                                                      int n_tiles, int64_t capacity, int64_t* __restrict__ K_out,
@@ -704,10 +701,6 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(uint32_t* __restrict__ tile
 // before it.  A single workgroup takes 9 us a round (its loads, two barriers a round and the scan are
 // one chain): the 25,800 tiles and 15,600 segments of an 8-view 1200x680 window took 29 us, 10 (5 + 5)
 // now; one round, a view of 1200x680, is faster in the one launch (8 us).
-constexpr int kScanChunk = 1024;
-
-static inline int scan_chunks(int n) { return (n + kScanChunk - 1) / kScanChunk; }
-
 __global__ __launch_bounds__(kScanChunk) void k_scan_sums(const uint32_t* __restrict__ tile_cnt, int n_tiles,
                                                           const uint32_t* __restrict__ vis_cnt, int n_segments,
                                                           unsigned long long* __restrict__ tile_sum,
@@ -1301,16 +1294,15 @@ hipError_t launch_bin(const tsr_scene_dev& sc, const float* poses, const ViewTab
   uint32_t* vis_dense = reinterpret_cast<uint32_t*>(ws + L.vis_dense);
   const int n_seg = (int)proj_segments(nf, vt.n_views);
   const int64_t scan_cap = sort ? L.capacity : (int64_t)0x7fffffffffffffffll;
-  if (vt.n_tiles <= kScanRound && n_seg <= kScanRound) {
+  if (!scan_in_chunks(vt.n_tiles, n_seg)) {
     TSR_LAUNCH("scan_tiles", k_scan_tiles, dim3(2), dim3(1024), 0, st, tile_cnt, ranges, vt.n_tiles, scan_cap, K, overflow,
                vis_cnt, vis_off, vis_total, n_seg, long_cnt, long_list);
   } else {
-    // the chunks' sums lie where later launches write: the tile order (4 bytes a tile, written beside the
-    // sorts) and the dense visible list (4 bytes a pair, written by the emission); both are 256-byte
-    // aligned parts, so there is room for a table of one chunk too
-    unsigned long long* tile_sum = reinterpret_cast<unsigned long long*>(ws + L.order);
-    unsigned long long* seg_sum = reinterpret_cast<unsigned long long*>(vis_dense);
-    const int tc = scan_chunks(vt.n_tiles), sch = scan_chunks(n_seg);
+    // the chunks' sums have a region of their own: a count (no emission or sort after it) of the poses that
+    // the workspace is binned for leaves the tile order and the dense visible list as they are
+    const int tc = (int)scan_chunks(vt.n_tiles), sch = (int)scan_chunks(n_seg);
+    unsigned long long* tile_sum = reinterpret_cast<unsigned long long*>(ws + L.scan_sums);
+    unsigned long long* seg_sum = tile_sum + tc;
     TSR_LAUNCH("scan_sums", k_scan_sums, dim3(tc + sch), dim3(kScanChunk), 0, st, tile_cnt, vt.n_tiles, vis_cnt, n_seg,
                tile_sum, seg_sum, tc);
     // (without segments nothing else writes their total)

@@ -46,6 +46,8 @@ struct WsLayout {
   size_t vis_cnt;                  // uint32 [NB]: visible (view, face) pairs of each visible-list segment
   size_t vis_off;                  // uint32 [NB]: exclusive scan of vis_cnt
   size_t vis_total;                // uint32: total visible (view, face) pairs
+  size_t scan_sums;                // uint64: sums of the tile counts' and then of the segment counts' chunks
+                                   // (tables of more than kScanRound entries only)
   size_t vis_list;                 // VisEntry [NB][256]: the visible (view, face) pairs of segment b
                                    // (first vis_cnt[b] entries)
   size_t vis_dense;                // uint32 [V*M]: the same ids, compacted (first vis_total entries)
@@ -72,6 +74,14 @@ inline int64_t proj_segments(int64_t n_pairs, int n_views) {
   const int64_t r = proj_rounds(n_views);
   return r * ((n_pairs + r * kProjBlock - 1) / (r * kProjBlock));
 }
+// Tile counts and visible-list segments are scanned by one workgroup up to kScanRound entries (one round
+// of kScanPer consecutive entries a thread: with 12 the 128 registers of a 1024-thread workgroup
+// spill), larger tables of either over chunks of kScanChunk.
+constexpr int kScanPer = 10;
+constexpr int kScanRound = 1024 * kScanPer;
+constexpr int kScanChunk = 1024;
+inline int64_t scan_chunks(int64_t n) { return (n + kScanChunk - 1) / kScanChunk; }
+inline bool scan_in_chunks(int64_t n_tiles, int64_t n_segments) { return n_tiles > kScanRound || n_segments > kScanRound; }
 constexpr int kRegSortMax = 1024;      // tile lists up to this length are sorted in registers
 constexpr int kWaveSortMax = 512;      // ... by one wave (longer ones by a whole workgroup)
 constexpr int kSmallTiles = 4;         // faces overlapping at most this many tiles record their slots

@@ -77,7 +77,6 @@ def tune(rast, poses, target_color, target_depth, reps: int = 5, candidates=CAND
     import torch
 
     rast.bin_and_sort(poses)
-    n_pairs = rast.count(poses)
     loss = torch.zeros(rast.n_views, device="cuda")
     grads = rast.grad_buffers()
     times: Dict[str, float] = {}

@@ -86,10 +86,16 @@ static __host__ __device__ inline int split_items(const ViewTable& vt) {
   return vt.n_views == 1 && vt.n_tiles >= kSplitTiles ? min(kSplitMax, vt.n_tiles / 8) : 0;
 }
 
+// Entry i of the longest-first order (a permutation of the tile ids, built with the binning); -1 for an
+// entry that is no tile (never from a valid binning).
+__device__ __forceinline__ int order_tile(const int* __restrict__ order, int i, int n_tiles) {
+  const int t = order[i];
+  return t >= 0 && t < n_tiles ? t : -1;
+}
+
 // Item i of a launch (ONE: of a single view): without an order the XCD-interleaved tile ids (i: the workgroup); with the
-// longest-first order (the permutation of the tile ids built with the binning; an entry outside
-// [0, n_tiles) gives no tile) first the second halves of its first split_items tiles (none
-// where the tile is not split), then every tile, whole or its first half.
+// longest-first order first the second halves of its first split_items tiles (none where the tile is
+// not split), then every tile, whole or its first half.
 template <bool ONE>
 __device__ __forceinline__ Item item_at(int i, const ViewTable& vt, const int* __restrict__ order,
                                         const uint32_t* __restrict__ ranges) {
@@ -97,8 +103,8 @@ __device__ __forceinline__ Item item_at(int i, const ViewTable& vt, const int* _
   const int n_tiles = vt.n_tiles, ns = ONE ? split_items(vt) : 0;
   const int pos = i < ns ? i : i - ns;
   if (pos >= n_tiles) return it;
-  const int t = order[pos];
-  if (t < 0 || t >= n_tiles) return it;
+  const int t = order_tile(order, pos, n_tiles);
+  if (t < 0) return it;
   if (pos < ns) it.split = ranges[2 * t + 1] - ranges[2 * t] > max(kSplitMin, ranges[2 * n_tiles - 1] / kSplitDiv);
   it.half = i < ns ? 1 : 0;
   if (it.half == 0 || it.split) it.tile = t;
@@ -1112,13 +1118,13 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       if (item >= vt.n_tiles + (ONE && order ? split_items(vt) : 0)) break;
       if constexpr (ONE) {
         it = order ? item_at<ONE>(item, vt, order, ranges) : Item{item, 0, false};
-        if (it.tile < 0) continue;
       } else {
-        it = Item{order ? order[item] : item, 0, false};
+        it = Item{order ? order_tile(order, item, vt.n_tiles) : item, 0, false};
       }
+      if (it.tile < 0) continue;
     } else {
       if constexpr (ONE) it = item_of_block<ONE>(vt, order, ranges);
-      else it = Item{order ? order[blockIdx.x] : tile_of_block(vt.n_tiles), 0, false};     // (grid: n_tiles)
+      else it = Item{order ? order_tile(order, (int)blockIdx.x, vt.n_tiles) : tile_of_block(vt.n_tiles), 0, false};     // (grid: n_tiles)
       if (it.tile < 0) break;
     }
     TileCtx c;

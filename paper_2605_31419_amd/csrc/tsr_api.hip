@@ -143,7 +143,8 @@ WsLayout layout(const ViewTable& vt, int64_t cap) {
   o = 256;
   L.pose_acc = o; o = align_up(o + sizeof(double) * tsr::kSumCopies * 6 * vt.n_views);
   L.loss_acc = o; o = align_up(o + sizeof(double) * tsr::kSumCopies * vt.n_views);
-  L.loss_part = o; o = align_up(o + sizeof(float) * tsr::kTileParts * vt.n_tiles);
+  L.loss_part = o; o = align_up(o + sizeof(float) * tsr::kTileQuads * vt.n_tiles);
+  L.half_part = o; o = align_up(o + sizeof(float) * tsr::kNormalPart * tsr::kTileQuads * tsr::split_items(vt));
   L.counts = o; o = align_up(o + sizeof(uint32_t) * nf);
   L.records = o; o = align_up(o + sizeof(float) * tsr::kRecDwords * nf);
   L.grad_acc = o; o = align_up(o + sizeof(tsr::acc_t) * tsr::kGradDwords * nf);

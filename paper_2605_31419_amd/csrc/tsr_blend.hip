@@ -57,6 +57,7 @@ struct Item {
   int tile;              // -1: nothing
   int half;
   bool split;
+  int slot;              // of a second half, split or not: its place in the table of second halves' sums
 };
 
 // Long tiles are split between two workgroups: wave w then owns the left or right 8x4 half (four
@@ -75,16 +76,10 @@ struct Item {
 // backwards walk whole tiles.
 // One 1200x680 view of 1M faces: forward 73 -> 55 us, backward 128 -> 117, fused 161 -> 139, face
 // statistics 61 -> 48.
-constexpr int kSplitMax = 256;           // split tiles at most: the first of the longest-first order
 constexpr uint32_t kSplitDiv = 1536, kSplitMin = 128;
-constexpr int kSplitTiles = 128;         // tiles of the view from which on tiles are split
 
 // Whether a backward in this mode may split tiles.
 template <int SM> constexpr bool split_bwd() { return (SM & 8) == 0; }
-
-static __host__ __device__ inline int split_items(const ViewTable& vt) {
-  return vt.n_views == 1 && vt.n_tiles >= kSplitTiles ? min(kSplitMax, vt.n_tiles / 8) : 0;
-}
 
 // Entry i of the longest-first order (a permutation of the tile ids, built with the binning); -1 for an
 // entry that is no tile (never from a valid binning).
@@ -99,14 +94,13 @@ __device__ __forceinline__ int order_tile(const int* __restrict__ order, int i, 
 template <bool ONE>
 __device__ __forceinline__ Item item_at(int i, const ViewTable& vt, const int* __restrict__ order,
                                         const uint32_t* __restrict__ ranges) {
-  Item it{-1, 0, false};
   const int n_tiles = vt.n_tiles, ns = ONE ? split_items(vt) : 0;
   const int pos = i < ns ? i : i - ns;
+  Item it{-1, i < ns ? 1 : 0, false, i};
   if (pos >= n_tiles) return it;
   const int t = order_tile(order, pos, n_tiles);
   if (t < 0) return it;
   if (pos < ns) it.split = ranges[2 * t + 1] - ranges[2 * t] > max(kSplitMin, ranges[2 * n_tiles - 1] / kSplitDiv);
-  it.half = i < ns ? 1 : 0;
   if (it.half == 0 || it.split) it.tile = t;
   return it;
 }
@@ -114,7 +108,7 @@ __device__ __forceinline__ Item item_at(int i, const ViewTable& vt, const int* _
 template <bool ONE>
 __device__ __forceinline__ Item item_of_block(const ViewTable& vt, const int* __restrict__ order,
                                               const uint32_t* __restrict__ ranges) {
-  return order ? item_at<ONE>((int)blockIdx.x, vt, order, ranges) : Item{tile_of_block(vt.n_tiles), 0, false};
+  return order ? item_at<ONE>((int)blockIdx.x, vt, order, ranges) : Item{tile_of_block(vt.n_tiles), 0, false, 0};
 }
 
 // Kernel modes: the low three bits select the window exponent -- 1: sigma = 1, 2: sigma = 0.5,
@@ -142,6 +136,7 @@ struct NormalIn {
   const uint32_t* count;   // backward: [V] valid target pixels per view
   float* part;             // forward: [n_tiles * 4][8] per-wave sums (valid pixels, sum of
                            // 1 - N.N_bar, sum of N x N_bar)
+  float* half_part;        // forward: [split_items * 4][8] those of split tiles' second halves
   float w_norm;
   int64_t M;
 };
@@ -310,7 +305,7 @@ static_assert(span_batches(kSpan) * (kBatchVec * sizeof(float4) + kSlots * sizeo
               "a staged span fits the LDS budget");
 static_assert(kWaves * kWave == kBlock && kWaves == 4, "one wave per 8x8 quadrant of a 16x16 tile");
 static_assert(kGradDwords == 20, "the accumulator row that grad_lane addresses");
-static_assert(2 * kWaves == kTileParts, "loss sums: two slots per wave of a tile");
+static_assert(kWaves == kTileQuads, "loss and normal sums: one slot per wave of a tile");
 
 // One wave stages a batch: lane l takes face l's id, then its record in kRecParts loads that go
 // straight from memory to LDS (no registers, all in flight at once), and with the normal channels
@@ -930,14 +925,6 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
 
 // ---------------------------------------------------------------------------- kernels
 
-// The normal sums' slot of a wave: one per quadrant of a tile, two in a single view (an unsplit
-// tile's wave fills both).
-template <bool ONE>
-__device__ __forceinline__ int64_t normal_slot(const Item& it, int quad) {
-  const int64_t q = (int64_t)it.tile * kWaves + quad;
-  return ONE ? 2 * q + it.half : q;
-}
-
 // COOP (several views): the tile's list is staged cooperatively (one shared copy per workgroup, the four
 // quadrant waves in step), else per wave (four copies, each wave at its own pace).
 template <int SM, bool COOP>
@@ -950,7 +937,12 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const flo
                                                       NormalIn nin) {
   const int wv = threadIdx.x >> 6;
   const Item it = item_of_block<!COOP>(vt, order, ranges);
-  if (it.tile < 0) return;
+  if (it.tile < 0) {
+    // the second half of a tile that is not split
+    if (normal_mode<SM>() && it.half && threadIdx.x < kWaves * kNormalPart)
+      nin.half_part[(int64_t)it.slot * kWaves * kNormalPart + threadIdx.x] = 0.f;
+    return;
+  }
   TileCtx c;
   tile_ctx(vt, ranges, it, wv, c);
   FwdState s;
@@ -996,10 +988,10 @@ __global__ __launch_bounds__(kBlock, 5) void k_blend_fwd(ViewTable vt, const flo
     }
     const float tc = wave_sum(cnt), tl = wave_sum(l), t0 = wave_sum(r0), t1 = wave_sum(r1), t2 = wave_sum(r2);
     if ((threadIdx.x & 63) == 0) {
-      float4* pw = reinterpret_cast<float4*>(nin.part + kNormalPart * normal_slot<!COOP>(it, wv));
+      const int64_t slot = (int64_t)(it.half ? it.slot : it.tile) * kWaves + wv;
+      float4* pw = reinterpret_cast<float4*>((it.half ? nin.half_part : nin.part) + kNormalPart * slot);
       pw[0] = make_float4(tc, tl, t0, t1);
       pw[1] = make_float4(t2, 0.f, 0.f, 0.f);
-      if (!COOP && !it.split) pw[2] = pw[3] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
   if (!c.own) return;
@@ -1091,7 +1083,8 @@ struct SeedScale {
 
 // Fused training kernel (ONE: of a single view that may have split tiles): forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
 // images and runs in tsr_ssim.hip between a separate forward and backward), backward
-// walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant, half).
+// walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant), the second halves'
+// apart.
 // Five workgroups per CU (96 registers a lane): the records of two faces in flight.
 template <int SM, bool ONE>
 __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTable vt, const float* __restrict__ records,
@@ -1100,7 +1093,7 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
                                                         SeedScale scale, const float* __restrict__ tcolor,
                                                         const float* __restrict__ tdepth, float* __restrict__ color, float* __restrict__ depth,
                                                         float* __restrict__ trans, float* __restrict__ loss_part,
-                                                        acc_t* __restrict__ grad_acc, float* __restrict__ sig_acc,
+                                                        float* __restrict__ half_part, acc_t* __restrict__ grad_acc, float* __restrict__ sig_acc,
                                                         float* __restrict__ persp_acc,
                                                         const int* __restrict__ order, int* __restrict__ queue,
                                                         int persistent) {
@@ -1129,15 +1122,19 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       ++round;
       if (item >= vt.n_tiles + (ONE && order ? split_items(vt) : 0)) break;
       if constexpr (ONE) {
-        it = order ? item_at<ONE>(item, vt, order, ranges) : Item{item, 0, false};
+        it = order ? item_at<ONE>(item, vt, order, ranges) : Item{item, 0, false, 0};
       } else {
-        it = Item{order ? order_tile(order, item, vt.n_tiles) : item, 0, false};
+        it = Item{order ? order_tile(order, item, vt.n_tiles) : item, 0, false, 0};
       }
-      if (it.tile < 0) continue;
     } else {
       if constexpr (ONE) it = item_of_block<ONE>(vt, order, ranges);
-      else it = Item{order ? order_tile(order, (int)blockIdx.x, vt.n_tiles) : tile_of_block(vt.n_tiles), 0, false};     // (grid: n_tiles)
-      if (it.tile < 0) break;
+      else it = Item{order ? order_tile(order, (int)blockIdx.x, vt.n_tiles) : tile_of_block(vt.n_tiles), 0, false, 0};     // (grid: n_tiles)
+    }
+    if (it.tile < 0) {
+      // the second half of a tile that is not split
+      if (ONE && it.half && loss_part && threadIdx.x < kWaves) half_part[kWaves * it.slot + threadIdx.x] = 0.f;
+      if (persistent) continue;
+      break;
     }
     TileCtx c;
     tile_ctx(vt, ranges, it, quad, c);
@@ -1185,11 +1182,10 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
       if (trans && c.own) trans[c.pix] = s.T;
     }
     if (loss_part) {
-      // one plain store per (tile, quadrant, half); summed per view after the backward
+      // one plain store per wave; summed per view after the backward
       const float ws = wave_sum(lpix);
-      const int part = 2 * (kWaves * it.tile + quad) + it.half;
-      if (lane == 0) loss_part[part] = ws;
-      if (lane == 1 && !it.split) loss_part[part + 1] = 0.f;
+      float* to = ONE && it.half ? half_part + kWaves * it.slot : loss_part + (int64_t)kWaves * it.tile;
+      if (lane == 0) to[quad] = ws;
     }
     if (ONE && it.split)
       backward_walk<SM, true, ONE, ONE>(c, records, pairs, sigma, s.last, s.Tb, pg, srec, sface, sint, grad_acc, sig_acc,
@@ -1225,25 +1221,27 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
                                                   const float* __restrict__ records, acc_t* grad_acc,
                                                   const float* __restrict__ persp_acc, int mid,
                                                   double* __restrict__ pose_acc, int want_vertices,
-                                                  const float* __restrict__ loss_part, double* __restrict__ loss_acc) {
+                                                  const float* __restrict__ loss_part,
+                                                  const float* __restrict__ half_part, int n_half,
+                                                  double* __restrict__ loss_acc) {
   const bool persp = persp_acc != nullptr;        // perspective-correct records
   __shared__ double s_pose[TSR_MAX_VIEWS * 6];    // this workgroup's pose sums, per view
   for (int k = threadIdx.x; k < TSR_MAX_VIEWS * 6; k += blockDim.x) s_pose[k] = 0.0;
   __syncthreads();
   if (loss_part) {
-    // per-view loss: each thread adds one tile's eight parts; waves whose tiles all
-    // belong to one view (all but at most one wave per view boundary) add one FP64 atomic
+    // per-view loss: each thread adds the four parts of one tile or (a single view) second half; waves whose
+    // tiles all belong to one view (all but at most one wave per view boundary) add one FP64 atomic
     const int lane = threadIdx.x & 63;
-    for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < vt.n_tiles; t0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t n_parts = (int64_t)vt.n_tiles + n_half;
+    for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < n_parts; t0 += (int64_t)gridDim.x * blockDim.x) {
       const int64_t t = t0 + threadIdx.x;
       double x = 0.0;
       int v = -1;
-      if (t < vt.n_tiles) {
-        const float4 q = reinterpret_cast<const float4*>(loss_part)[2 * t];
-        const float4 r = reinterpret_cast<const float4*>(loss_part)[2 * t + 1];
-        x = (((double)q.x + (double)q.y) + ((double)q.z + (double)q.w)) +
-            (((double)r.x + (double)r.y) + ((double)r.z + (double)r.w));
-        v = view_of_tile(vt, (int)t);
+      if (t < n_parts) {
+        const float4 q = t < vt.n_tiles ? reinterpret_cast<const float4*>(loss_part)[t]
+                                        : reinterpret_cast<const float4*>(half_part)[t - vt.n_tiles];
+        x = ((double)q.x + (double)q.y) + ((double)q.z + (double)q.w);
+        v = t < vt.n_tiles ? view_of_tile(vt, (int)t) : 0;
       }
       const int v0 = __shfl(v, 0, 64);
       double* lc = loss_acc + (int64_t)(blockIdx.x % kSumCopies) * vt.n_views;
@@ -1488,14 +1486,14 @@ __device__ __forceinline__ void write_sums(const ViewTable& vt, const double* __
   }
 }
 
-// Per-view L1 loss: FP64 sum of the kTileParts parts of the view's tiles, by one
-// workgroup of kBlock threads (every thread calls).
+// Per-view L1 loss: FP64 sum of the kTileQuads parts of the view's tiles, by one
+// workgroup of kBlock threads (every thread calls).  For scenes without faces: no tile is split.
 __device__ void reduce_view_losses(const ViewTable& vt, const float* __restrict__ loss_part, float* __restrict__ loss) {
   __shared__ double red[kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int v = 0; v < vt.n_views; ++v) {
-    const int64_t p0 = (int64_t)kTileParts * vt.v[v].tile_off;
-    const int np = kTileParts * vt.v[v].tiles_x * vt.v[v].tiles_y;
+    const int64_t p0 = (int64_t)kTileQuads * vt.v[v].tile_off;
+    const int np = kTileQuads * vt.v[v].tiles_x * vt.v[v].tiles_y;
     double x = 0.0;
     for (int i = threadIdx.x; i < np; i += blockDim.x) x += (double)loss_part[p0 + i];
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
@@ -1986,7 +1984,7 @@ hipError_t launch_forward(const ViewTable& vt, const tsr_params& p, const WsLayo
   NormalIn nin{};
   if (nc)
     nin = NormalIn{reinterpret_cast<const float4*>(nc->face_normal), nullptr, nc->map, nc->poses, nc->target,
-                   nullptr, nc->part, nc->w_norm, vt.n_faces};
+                   nullptr, nc->part, reinterpret_cast<float*>(ws + L.half_part), nc->w_norm, vt.n_faces};
   const bool coop = separate_coop(vt);
 #define TSR_FWD(S)                                                                                 \
   {                                                                                                \
@@ -2022,6 +2020,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
   float* sig_acc = vt.face_sigma ? reinterpret_cast<float*>(ws + L.sig_acc) : nullptr;
   float* persp_acc = p.perspective ? reinterpret_cast<float*>(ws + L.persp_acc) : nullptr;
   float* loss_part = reinterpret_cast<float*>(ws + L.loss_part);
+  float* half_part = reinterpret_cast<float*>(ws + L.half_part);
   double* loss_acc = reinterpret_cast<double*>(ws + L.loss_acc);
   const int64_t nf = (int64_t)vt.n_views * vt.n_faces;
   const int* order = nullptr;
@@ -2048,7 +2047,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
     NormalIn nin{};
     if (nc)
       nin = NormalIn{reinterpret_cast<const float4*>(nc->face_normal), reinterpret_cast<float4*>(nc->grad), nullptr,
-                     nc->poses, nc->target, nc->count, nullptr, nc->w_norm, vt.n_faces};
+                     nc->poses, nc->target, nc->count, nullptr, nullptr, nc->w_norm, vt.n_faces};
 #define TSR_BWD(S)                                                                                 \
   {                                                                                                \
     auto kb = coop ? k_blend_bwd<S, true> : k_blend_bwd<S, false>;                                 \
@@ -2072,7 +2071,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
       scale.d[v] = p.w_depth / hw;
     }
     for (int v = vt.n_views; v < TSR_MAX_VIEWS; ++v) scale.c[v] = scale.d[v] = 0.f;
-#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", (one ? k_train_fused<S, split_bwd<S>()> : k_train_fused<S, false>), grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
+#define TSR_TRAIN(S) TSR_LAUNCH("train_fused", (one ? k_train_fused<S, split_bwd<S>()> : k_train_fused<S, false>), grid, block, 0, st, vt, records, pairs, ranges, p.sigma, p.t_min, scale, tcolor, tdepth, color, depth, trans, loss ? loss_part : nullptr, half_part, grad_acc, sig_acc, persp_acc, order, queue, sched.persistent)
     TSR_MODE_SWITCH(sm, TSR_TRAIN)
 #undef TSR_TRAIN
   }
@@ -2091,7 +2090,7 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
     const dim3 fgrid(std::min<unsigned>(grid_for(nf, 256), 2048u));
     TSR_LAUNCH("face_bwd", k_face_bwd, fgrid, dim3(256), 0, st, sc, poses, vt, vis_total, vis_dense, records,
                grad_acc, persp_acc, mid ? 1 : 0, grad_pose ? pose_acc : nullptr, want_vertices ? 1 : 0, loss ? loss_part : nullptr,
-               loss_acc);
+               half_part, order ? n_items - vt.n_tiles : 0, loss_acc);
     if (want_gather)
       TSR_LAUNCH("vertex_gather", k_vertex_gather, dim3(grid_for(vt.n_faces, 256)), dim3(256), 0, st, sc, vt, counts,
                  grad_acc, sig_acc, grad_pos, grad_col, grad_opa, pose_acc, grad_pose, loss_acc, loss);

@@ -31,7 +31,9 @@ struct WsLayout {
   size_t hdr_sticky;               // uint32: some binning since the last tsr_check overflowed
   size_t pose_acc;                 // double [kSumCopies][V][6]
   size_t loss_acc;                 // double [kSumCopies][V]
-  size_t loss_part;                // float [T][8]: L1 loss of each (tile, 8x8 quadrant, half)
+  size_t loss_part;                // float [T][4]: L1 loss of each (tile, 8x8 quadrant)
+  size_t half_part;                // float [split_items][4][kNormalPart]: sums of the split tiles' second
+                                   // halves, a wave each: losses ([split_items][4]) or normal sums
   size_t counts;                   // uint32 [V*M]
   size_t records;                  // float  [V*M][24]
   size_t grad_acc;                 // float  [V*M][20]
@@ -87,7 +89,7 @@ constexpr int kWaveSortMax = 512;      // ... by one wave (longer ones by a whol
 constexpr int kSmallTiles = 4;         // faces overlapping at most this many tiles record their slots
 constexpr int kTileCntStride = 4;     // dwords per tile in the tile-counter array
 constexpr uint32_t kSkipSlot = 0xffffffffu;   // recorded slot of a tile the tight binning leaves out
-constexpr int kTileParts = 8;          // partial sums of a 16x16 tile: two per 8x8 quadrant (one blend wave each)
+constexpr int kTileQuads = 4;          // 8x8 quadrants of a 16x16 tile (one blend wave each)
 constexpr int kNormalPart = 8;         // floats of normal-loss sums per blend wave (mapping step)
 
 // What the emission of one visible (view, face) pair needs, written by the projection in the
@@ -174,6 +176,15 @@ void prof_end(int token, const char* name, hipStream_t st);
     ::tsr::prof_end(tsr_tok_, name, st);                                      \
   } while (0)
 
+// Second halves in a launch over the tiles of `vt` (where and why tiles are split: tsr_blend.hip): one for
+// each of the first tiles of the longest-first order, whether that tile is then split or not.
+constexpr int kSplitMax = 256;           // split tiles at most
+constexpr int kSplitTiles = 128;         // tiles of the view from which on tiles are split
+
+static __host__ __device__ inline int split_items(const ViewTable& vt) {
+  return vt.n_views == 1 && vt.n_tiles >= kSplitTiles ? min(kSplitMax, vt.n_tiles / 8) : 0;
+}
+
 hipError_t launch_ws_init(char* ws, hipStream_t st);
 
 hipError_t launch_bin(const tsr_scene_dev& sc, const float* poses, const ViewTable& vt, const tsr_params& p,
@@ -183,7 +194,8 @@ hipError_t launch_bin(const tsr_scene_dev& sc, const float* poses, const ViewTab
 // face's world unit normal composited like a colour constant over the face.  face_normal and
 // grad are [M][4] floats (x, y, z, 0) per face, summed over the views in grad (which the
 // caller zero-fills); map (forward, may be null: N in the camera frame) and target are packed
-// like colour; part (forward) holds 8 floats per wave of each tile (kernel-written), count
+// like colour; part (forward) holds 8 floats per wave of each tile (kernel-written; those of split tiles'
+// second halves are in the workspace), count
 // (backward) the valid target pixels of each view.
 struct NormalChannels {
   const float* face_normal;

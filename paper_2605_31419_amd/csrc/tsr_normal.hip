@@ -374,7 +374,7 @@ MappingScratch mapping_scratch(size_t ssim_bytes, int64_t n_faces, int64_t n_til
   z.nrm = up(ssim_bytes);
   z.gacc = up(z.nrm + 16 * (size_t)n_faces);
   z.part = up(z.gacc + 16 * (size_t)n_faces);
-  z.count = up(z.part + sizeof(float) * kNormalPart * kTileParts * (size_t)n_tiles);
+  z.count = up(z.part + sizeof(float) * kNormalPart * kTileQuads * (size_t)n_tiles);
   z.acc = up(z.count + sizeof(uint32_t) * TSR_MAX_VIEWS);
   z.total = up(z.acc + sizeof(double) * 4 * TSR_MAX_VIEWS);
   return z;
@@ -382,22 +382,20 @@ MappingScratch mapping_scratch(size_t ssim_bytes, int64_t n_faces, int64_t n_til
 
 // Per view, the forward's per-wave normal-loss sums in FP64: the valid-pixel count, the loss
 // sum, and the rotation term sum_p N x dE/dN = -(w_norm / count) sum_p N x N_bar, in the layout
-// k_normal_finish reads.  One 256-thread workgroup per view, four slots per thread in flight;
-// overwrites count and acc.
+// k_normal_finish reads; overwrites count and acc.  `half` holds the slots of a single view's second halves
+// (n_half waves).
 // One workgroup per view: its length is the latency of its loads, so it has 1,024 threads with four
 // slots each in flight (5 views of 1001x680: 18 us with 256 threads, 12 now).
 constexpr int kReduceBlock = 1024;
 
 __global__ __launch_bounds__(kReduceBlock) void k_normal_reduce(ViewTable vt, const float* __restrict__ part,
-                                                                float w_norm, uint32_t* __restrict__ count,
+                                                                const float* __restrict__ half, int n_half, float w_norm, uint32_t* __restrict__ count,
                                                                 double* __restrict__ acc) {
   __shared__ double red[5][kReduceBlock / 64];
   const int v = blockIdx.x;
   const ViewDesc vd = vt.v[v];
-  // slots per tile: one for each of its four waves, two in a single view (split tiles)
-  const int per = vt.n_views == 1 ? kTileParts : kTileParts / 2;
-  const int64_t w0 = (int64_t)vd.tile_off * per;
-  const int64_t w1 = w0 + (int64_t)vd.tiles_x * vd.tiles_y * per;
+  const int64_t w0 = (int64_t)vd.tile_off * kTileQuads;
+  const int64_t wt = w0 + (int64_t)vd.tiles_x * vd.tiles_y * kTileQuads, w1 = wt + n_half;
   double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   static_assert(kNormalPart == 8, "a slot is two float4");
   for (int64_t base = w0; base < w1; base += 4 * kReduceBlock) {
@@ -405,7 +403,7 @@ __global__ __launch_bounds__(kReduceBlock) void k_normal_reduce(ViewTable vt, co
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t w = base + u * kReduceBlock + threadIdx.x;
-      const float4* p = reinterpret_cast<const float4*>(part + kNormalPart * w);
+      const float4* p = reinterpret_cast<const float4*>(w < wt ? part + kNormalPart * w : half + kNormalPart * (w - wt));
       a[u] = w < w1 ? p[0] : make_float4(0.f, 0.f, 0.f, 0.f);
       b[u] = w < w1 ? p[1] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
@@ -465,7 +463,8 @@ hipError_t launch_train_mapping(const tsr_scene_dev& sc, const float* poses, con
                           part, w_norm};
   hipError_t e = launch_forward(vt, p, L, ws, color, depth, trans, st, &fc);
   if (e != hipSuccess) return e;
-  TSR_LAUNCH("normal_reduce", k_normal_reduce, dim3(vt.n_views), dim3(kReduceBlock), 0, st, vt, part, w_norm, count, acc);
+  TSR_LAUNCH("normal_reduce", k_normal_reduce, dim3(vt.n_views), dim3(kReduceBlock), 0, st, vt, part,
+             reinterpret_cast<const float*>(ws + L.half_part), kTileQuads * split_items(vt), w_norm, count, acc);
   float *gc = nullptr, *gd = nullptr;
   e = launch_photo_seeds(t, color, target_color, depth, target_depth, w_ssim, p.w_color, p.w_depth, loss, scratch,
                          &gc, &gd, st);

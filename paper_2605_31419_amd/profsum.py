@@ -20,10 +20,23 @@ COPY_BYTES = 256 << 20
 
 
 def _short(name: str) -> str:
-    m = re.search(r"(k_[a-z_0-9]+)(<\d+>)?", name or "")
+    """A kernel's name with its template arguments, which tell the modes and the single- and
+    several-view builds apart, without spaces."""
+    m = re.search(r"(k_[a-z_0-9]+)(<[^<>]*>)?", name or "")
     if m:
-        return m.group(1) + (m.group(2) or "")
+        return m.group(1) + (m.group(2) or "").replace(" ", "")
     return (name or "")[:40]
+
+
+def instantiation(names, kernel: str) -> str:
+    """The one of `names` that `kernel` stands for: itself, or without template arguments the only
+    instantiation among them."""
+    found = sorted({n for n in names if n == kernel or n.split("<")[0] == kernel})
+    if kernel in found:
+        return kernel
+    if len(found) != 1:
+        raise SystemExit(f"{kernel}: {'no launches' if not found else 'several kernels: ' + ', '.join(found)}")
+    return found[0]
 
 
 def _rows(db, table):
@@ -72,11 +85,12 @@ def traffic(fetch_db, write_db, kernel):
     copy_f = max(copies_f)
     ff = COPY_BYTES / (copy_f * 1024.0)
     fw = COPY_BYTES / (copy_w * 1024.0)
+    kernel = instantiation([k for k, _ in f], kernel)
     kf = f[(kernel, "FETCH_SIZE")]
     kw = w[(kernel, "WRITE_SIZE")]
     fb = sum(kf) / len(kf) * 1024.0 * ff
     wb = sum(kw) / len(kw) * 1024.0 * fw
-    return {"fetch_factor": ff, "write_factor": fw, "fetch_bytes": fb, "write_bytes": wb,
+    return {"kernel": kernel, "fetch_factor": ff, "write_factor": fw, "fetch_bytes": fb, "write_bytes": wb,
             "dispatches": (len(kf), len(kw))}
 
 
@@ -86,7 +100,8 @@ def main():
     ap.add_argument("db", nargs="?")
     ap.add_argument("--fetch")
     ap.add_argument("--write")
-    ap.add_argument("--kernel", action="append", help="kernel name (repeatable); default k_train_fused")
+    ap.add_argument("--kernel", action="append", help="kernel name, with template arguments where several instantiations ran "
+                    "(repeatable); default k_train_fused")
     a = ap.parse_args()
     if a.mode == "kernels":
         print_kernels(a.db)
@@ -101,7 +116,7 @@ def main():
             if i == 0:
                 print(f"calibration: fetched bytes = {t['fetch_factor']:.3f} x FETCH_SIZE, "
                       f"written bytes = {t['write_factor']:.3f} x WRITE_SIZE")
-            print(f"traffic: kernel={k} fetch_bytes={t['fetch_bytes']:.0f} write_bytes={t['write_bytes']:.0f} "
+            print(f"traffic: kernel={t['kernel']} fetch_bytes={t['fetch_bytes']:.0f} write_bytes={t['write_bytes']:.0f} "
                   f"sources={fp}")
 
 

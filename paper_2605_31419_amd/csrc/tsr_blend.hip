@@ -728,7 +728,10 @@ __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __r
   constexpr int kStage = COOP ? SPAN : kBatch;      // faces staged at once
   int top = wlast;
   if (COOP && c.end - c.start <= (uint32_t)kStage) {
-    top = (int)c.end - 1;                           // one span: staged whole, whatever was blended
+    // one span, staged whole, whatever was blended; while the forward's is still there no barrier is ahead
+    // of a wave that blended none of it (most waves of a map of few faces)
+    if (wlast < (int)c.start && (staged == c.start || c.start == c.end)) return;
+    top = (int)c.end - 1;
   } else if constexpr (COOP) {
     if (threadIdx.x == 0) sint[0] = -1;
     __syncthreads();
@@ -1081,7 +1084,8 @@ struct SeedScale {
   float c[TSR_MAX_VIEWS], d[TSR_MAX_VIEWS];
 };
 
-// Fused training kernel (ONE: of a single view that may have split tiles): forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
+// Fused training kernel (ONE: of a single view that may have split tiles, in the longest-first order):
+// forward walk, L1 seeds of eqs. 8-10 (the D-SSIM term needs whole
 // images and runs in tsr_ssim.hip between a separate forward and backward), backward
 // walk, without leaving the workgroup.  Also writes the loss of each (tile, quadrant), the second halves'
 // apart.
@@ -1120,14 +1124,14 @@ __global__ __launch_bounds__(kBlock, SM == 8 ? 4 : 5) void k_train_fused(ViewTab
         item = s_item;
       }
       ++round;
-      if (item >= vt.n_tiles + (ONE && order ? split_items(vt) : 0)) break;
+      if (item >= vt.n_tiles + (ONE ? split_items(vt) : 0)) break;
       if constexpr (ONE) {
-        it = order ? item_at<ONE>(item, vt, order, ranges) : Item{item, 0, false, 0};
+        it = item_at<ONE>(item, vt, order, ranges);
       } else {
         it = Item{order ? order_tile(order, item, vt.n_tiles) : item, 0, false, 0};
       }
     } else {
-      if constexpr (ONE) it = item_of_block<ONE>(vt, order, ranges);
+      if constexpr (ONE) it = item_at<ONE>((int)blockIdx.x, vt, order, ranges);
       else it = Item{order ? order_tile(order, (int)blockIdx.x, vt.n_tiles) : tile_of_block(vt.n_tiles), 0, false, 0};     // (grid: n_tiles)
     }
     if (it.tile < 0) {
@@ -2038,8 +2042,10 @@ hipError_t launch_backward(const tsr_scene_dev& sc, const float* poses, const Vi
   const int sm = sigma_mode(vt, p);
   const int n_items = vt.n_tiles + (p.perspective ? 0 : split_items(vt));
   const bool coop = separate_coop(vt);
-  // which moments the walks take (as the kernels chosen below are built)
-  const bool one = split_items(vt) > 0;
+  // The fused kernel with the split walks only where a schedule gives it the order (without, no tile is
+  // split: a 1199x679 view of 5,000 faces took 60.9 us a step with it and takes 58.8 without), and which
+  // moments the walks take (as the kernels chosen below are built).
+  const bool one = order && split_items(vt) > 0;
   const bool mid = !p.perspective && (fused_train ? one : !coop);
   if (!fused_train) {
     const dim3 grid(n_items);

@@ -147,7 +147,8 @@ __device__ __forceinline__ float window_pow(float rho, float sigma) {
   if constexpr (exp_mode<SM>() == 1) return rho;
   else if constexpr (exp_mode<SM>() == 2) return __builtin_sqrtf(rho);
   else if constexpr (exp_mode<SM>() == 3) return rho * rho;
-  else return rho > 0.f ? exp2f(sigma * log2f(rho)) : 0.f;       // (an empty record's sigma is 0)
+  // (the ends apart: an empty record's sigma is 0, and an infinite sigma has 1 at the incentre)
+  else return rho > 0.f ? (rho < 1.f ? exp2f(sigma * log2f(rho)) : 1.f) : 0.f;
 }
 
 // The exponent a face is evaluated with: its record's in mode 4, else the launch's.

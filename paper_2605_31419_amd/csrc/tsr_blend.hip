@@ -541,6 +541,7 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
           lv = live(s.T, t_min);
         };
         blend(A.f0, X.f0, Y.f0, NX.f0, NY.f0, i0);
+        if (ballot(lv) == 0ull) break;          // (the second face is not visited)
         blend(A.f1, X.f1, Y.f1, NX.f1, NY.f1, i1);
         const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
         if (done) break;
@@ -575,6 +576,7 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
       load_rec(sr, j1, r1);
       for (;;) {
         visit(r0, j0);
+        if (ballot(lv) == 0ull) break;          // (the second face is not visited)
         j0 = first_bit(mask);
         __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
         load_rec(sr, j0, r0);

@@ -147,8 +147,11 @@ __device__ __forceinline__ float window_pow(float rho, float sigma) {
   if constexpr (exp_mode<SM>() == 1) return rho;
   else if constexpr (exp_mode<SM>() == 2) return __builtin_sqrtf(rho);
   else if constexpr (exp_mode<SM>() == 3) return rho * rho;
-  // (the ends apart: an empty record's sigma is 0, and an infinite sigma has 1 at the incentre)
-  else return rho > 0.f ? (rho < 1.f ? exp2f(sigma * log2f(rho)) : 1.f) : 0.f;
+  else {
+    // the ends apart: an empty record's sigma is 0, and an infinite sigma has 1 at the incentre
+    const float x = exp2f(sigma * log2f(rho)), y = rho < 1.f ? x : 1.f;
+    return rho > 0.f ? y : 0.f;
+  }
 }
 
 // The exponent a face is evaluated with: its record's in mode 4, else the launch's.

@@ -211,7 +211,11 @@ __device__ __forceinline__ void write_record(const FaceAttr& at, const FaceSetup
   rec[kRecZ] = (float)f.zf;
   rec[kRecU0] = (float)f.u0;          // exact: |u0| < 2^24
   rec[kRecV0] = (float)f.v0;
-  rec[kRecMid] = __int_as_float((f.u0 + f.u1) | ((f.v0 + f.v1) << 16));    // both below 2^15
+  float csum = 0.f;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) csum += fabsf(rec[kRecCol + k]);
+  const uint32_t odd = csum <= 3.402823466e38f ? 0u : 0x80000000u;
+  rec[kRecMid] = __uint_as_float((uint32_t)(f.u0 + f.u1) | ((uint32_t)(f.v0 + f.v1) << 16) | odd);    // both below 2^15
   rec[kRecSigma] = at.sigma;
   if (at.persp) {
     // denominator plane W = sum_k lambda_opp(k) / z_opp(k) (1 / depth of the face's plane)

@@ -361,6 +361,7 @@ __device__ __forceinline__ void stage_span(const float* __restrict__ records, co
 // the magnitude of the terms) exceeds the FP32 rounding of both evaluations.
 // Perspective-correct records do not hold the rectangle's end: the edge test then runs over
 // the whole quadrant (still conservative).
+//   `odd` (if given) receives the faces of the mask whose colours are not finite.
 __device__ __forceinline__ void load_edges(const float4* srec, int j, float (&r)[12]) {
   static_assert(kRecEdge == 0, "the edge functions are the record's first nine dwords");
 #pragma unroll
@@ -374,9 +375,10 @@ __device__ __forceinline__ void load_edges(const float4* srec, int j, float (&r)
 }
 
 template <int SM>
-__device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec, int n, int bx, int by, int bw) {
+__device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec, int n, int bx, int by, int bw,
+                                                             unsigned long long* odd = nullptr) {
   const int j = threadIdx.x & 63;
-  bool hit = false;
+  bool hit = false, bad = false;
   if constexpr (persp_mode<SM>()) {
     if (j < n) {
       const float4 rc = srec[kRecU0 / 4 * kSlots + j];
@@ -394,13 +396,22 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
         const float margin = 1e-6f * (fabsf(a) * mx + fabsf(b) * my + fabsf(c)) + 1e-30f;
         hit = hit && !(emax < -margin);
       }
+      if (odd) {
+        // (no room in the record for a flag)
+        static_assert(kRecCol == 9, "the colours are dwords 9 to 17");
+        const float4 p = srec[2 * kSlots + j], q = srec[3 * kSlots + j], s = srec[4 * kSlots + j];
+        const float sum = fabsf(p.y) + fabsf(p.z) + fabsf(p.w) + fabsf(q.x) + fabsf(q.y) + fabsf(q.z) + fabsf(q.w) +
+                          fabsf(s.x) + fabsf(s.y);
+        bad = hit && !(sum <= 3.402823466e38f);
+      }
     }
+    if (odd) *odd = ballot(bad);
     return ballot(hit);
   }
   if (j < n) {
     const float4 rc = srec[kRecU0 / 4 * kSlots + j];
     const int mid = __float_as_int(rc.z);
-    const int u0 = (int)rc.x, v0 = (int)rc.y, u1 = (mid & 0xffff) - u0, v1 = (mid >> 16) - v0;
+    const int u0 = (int)rc.x, v0 = (int)rc.y, u1 = (mid & 0xffff) - u0, v1 = ((mid >> 16) & 0x7fff) - v0;
     const int xl = max(bx, u0), xh = min(bx + bw - 1, u1), yl = max(by, v0), yh = min(by + 7, v1);
     hit = xl <= xh && yl <= yh;
     if (hit) {
@@ -416,7 +427,9 @@ __device__ __forceinline__ unsigned long long batch_hit_mask(const float4* srec,
         hit = hit && !(emax < -margin);
       }
     }
+    bad = hit && mid < 0;
   }
+  if (odd) *odd = ballot(bad);
   return ballot(hit);
 }
 
@@ -470,7 +483,10 @@ __device__ __forceinline__ uint32_t where_any(uint32_t a, uint32_t x) {
 // transmittance just before it.  The faces of a batch's mask are taken two per round, and each
 // record is loaded from LDS a face ahead, while the other one of the pair is evaluated and
 // blended: a wave alone issues one instruction in about five cycles and waits 130 for a record,
-// and the waves of the longest tiles bound the kernel.
+// and the waves of the longest tiles bound the kernel.  Whether any pixel goes on is asked after both
+// faces of a pair (asked between them too, a lone tile's forward takes 123 ns a face instead of 107), so
+// the second may be evaluated, with weight 0, after every pixel has stopped: a face whose colours are
+// not finite, which 0 would not keep out of the image, is therefore never the second of a pair.
 template <int SM, bool COOP, bool SPLIT, int SPAN = kSpan>
 __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __restrict__ records,
                                              const uint64_t* __restrict__ pairs, float sigma, float t_min,
@@ -500,9 +516,14 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
     const uint32_t b0 = s0 + (uint32_t)h;
     const float4* sr = srec + h / kBatch * kBatchVec;
     const float4* sn = normal_mode<SM>() ? snrm + h / kBatch * kSlots : nullptr;
-    unsigned long long mask = batch_hit_mask<SM>(sr, n, c.bx, c.by, c.bw);
-    if (hits) hits[h / kBatch] = mask;
-    if (mask == 0ull) continue;
+    unsigned long long odd, rest = batch_hit_mask<SM>(sr, n, c.bx, c.by, c.bw, &odd);
+    if (hits) hits[h / kBatch] = rest;
+    // one piece, but for faces whose colours are not finite, which begin pieces of their own
+    for (; rest != 0ull && ballot(lv) != 0ull;) {
+    const unsigned long long later = odd & rest & (rest - 1);
+    const unsigned long long piece = later ? (later & -later) - 1 : ~0ull;
+    unsigned long long mask = rest & piece;
+    rest &= ~piece;
     if constexpr (SPLIT) {
       // a face per half of the wave; its alpha and channels to both halves (the first and third, second
       // and depth of each face side by side), blended in order there
@@ -544,7 +565,6 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
           lv = live(s.T, t_min);
         };
         blend(A.f0, X.f0, Y.f0, NX.f0, NY.f0, i0);
-        if (ballot(lv) == 0ull) break;          // (the second face is not visited)
         blend(A.f1, X.f1, Y.f1, NX.f1, NY.f1, i1);
         const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
         if (done) break;
@@ -579,7 +599,6 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
       load_rec(sr, j1, r1);
       for (;;) {
         visit(r0, j0);
-        if (ballot(lv) == 0ull) break;          // (the second face is not visited)
         j0 = first_bit(mask);
         __builtin_amdgcn_sched_barrier(0);      // the record's registers are free: reload them in place
         load_rec(sr, j0, r0);
@@ -592,6 +611,7 @@ __device__ __forceinline__ void forward_walk(const TileCtx& c, const float* __re
         const bool done = (j0 == kBatch) | (ballot(lv) == 0ull);
         if (done) break;
       }
+    }
     }
     }
   }
@@ -1327,9 +1347,9 @@ __global__ __launch_bounds__(256) void k_face_bwd(tsr_scene_dev sc, const float*
     // the point that the planes' moments are about: the record's anchor, or (mid) the rectangle's middle
     double U0 = (double)rec[kRecU0], V0 = (double)rec[kRecV0];
     if (mid) {
-      const int w = __float_as_int(rec[kRecMid]);
-      U0 = 0.5 * (double)(w & 0xffff);
-      V0 = 0.5 * (double)(w >> 16);
+      const uint32_t w = __float_as_uint(rec[kRecMid]);
+      U0 = 0.5 * (double)(w & 0xffffu);
+      V0 = 0.5 * (double)(w >> 16);              // (with the flag, as the walks)
     }
     double ca[3], cb[3], cc[3];       // edge coefficients a_k, b_k, c_k
     for (int k = 0; k < 3; ++k) {

@@ -28,7 +28,7 @@ enum RecordField : int {
   kRecU0 = 20,       // u0 as a float (an exact integer)
   kRecV0 = 21,       // v0 as a float (an exact integer)
   kRecMid = 22,      // int (u0 + u1) | (v0 + v1) << 16, (u1, v1) the rectangle's last pixel: twice its
-                     // middle (image sizes are at most 16384)
+                     // middle (image sizes are at most 16384); bit 31: a colour plane is not finite
   kRecSigma = 23,    // the face's window exponent sigma (eq. 3)
   kRecDwords = 24
 };

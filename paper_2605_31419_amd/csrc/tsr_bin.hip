@@ -565,11 +565,10 @@ __global__ __launch_bounds__(256, 4) void k_project(tsr_scene_dev sc, const floa
 
 // Two workgroups of 1024 threads, working independently: (0) exclusive scan of the
 // visible-face counts of the visible-list segments (offsets of the segments in the dense
-// visible list); (1) exclusive scan of the tile counts into ranges, pair total K, overflow check against the capacity (all
-// ranges empty on overflow), the small-face counts left in tile_cnt2 as the base of the
-// larger faces' emission cursors, and the list of tiles too long for the one-wave sort.  Both
+// visible list); (1) exclusive scan of the tile counts into ranges, pair total K, overflow check against
+// the capacity (all ranges empty on overflow), the small-face counts left in tile_cnt2 as the base of
+// the larger faces' emission cursors, and the list of tiles too long for the one-wave sort.  Both
 // scans run in rounds of kScanRound entries, each thread taking kScanPer consecutive ones.
-
 __global__ __launch_bounds__(1024) void k_scan_tiles(uint32_t* __restrict__ tile_cnt, uint32_t* __restrict__ ranges,
                                                      int n_tiles, int64_t capacity, int64_t* __restrict__ K_out,
                                                      uint32_t* __restrict__ overflow, const uint32_t* __restrict__ vis_cnt,
@@ -1120,7 +1119,7 @@ __device__ __forceinline__ void block_merge_sort(uint64_t* base, int n, uint64_t
 
 // Per-tile depth sort, ascending by (z bits, face), in one launch with two kinds of
 // workgroups: the first kLongBlocks are persistent over the list of tiles longer than
-// kWaveSortMax keys (built by k_scan_tiles), so they start first and overlap the rest; each
+// kWaveSortMax keys (built by the scan), so they start first and overlap the rest; each
 // remaining workgroup sorts four tiles, one wave each, in registers.
 //   Long lists of up to kRegSortMax keys are sorted in registers by the whole workgroup
 // (block_bitonic1024: 11.6 us for the launch at 1200x680 with 1M faces, whose longest list has 594

@@ -7,26 +7,19 @@
 // by that wave with one scalar test.  Face records are staged in LDS in batches of kBatch by
 // loads that go straight to LDS, and read by all lanes as broadcasts.
 //
-// What bounds the walks (1200x680 view of 1M faces, fused kernel): a wave alone on its SIMD issues
-// one instruction in about five cycles, so the longest tile's four waves take about 0.34 us per
-// listed face whatever else runs (594 faces: 151 us of a 156 us launch), and below that the number of
-// VALU instructions per visit.  The forward takes two faces per round, its records loaded a face
-// ahead and staged without registers (72 -> 84 VGPRs instead of 120); the backward evaluates the two
-// faces of a round in the two halves of the wave, two pixels a lane, so that one set of gradient sums
-// serves both.  Per listed face of the longest tile: forward 140 -> 115 ns, backward 315 -> 258 with
-// two faces one after the other and 226 in the two halves; the step 278 -> 244 -> 238 us, the 8-view
-// window of 500k faces 700 -> 641 -> 629 us, the photometric step 368 -> 335 -> 328 us, the 8-view
-// mapping step 2.28 -> 2.13 -> 2.09 ms and the face statistics (no backward) 139 -> 125 us.
-// (Both halves in the forward too, with eight waves of 8x4 pixels per tile, cut the longest tile's
-// walk to 97 + 157 ns per face, but twice the waves with their set-up and hit masks, and 1.4 times
-// the gradient atomics, made every case slower: mapping 2.53 ms.)
-//   Where lists are short (the 8-view window: 42 faces a tile, 12 visits a wave) a quarter of the
-// fused kernel's VALU instructions were outside the walks: 1,809 a wave, 462 of them in the set-up,
-// the hit masks, the seeds and the wave maximum.  The backward takes the masks that the forward
-// formed for the span still in LDS, the seeds' scales come from the host, the maximum goes by
-// DPP: window 629 -> 616 us, 640x480 tracking 542 -> 533 us for eight iterations.
-//   These are whole tiles; the long ones of a single view are split (Item), after which that view's
-// fused launch is bound by its VALU instructions too (594 faces: 116 us of 122).
+// What bounds the walks: their VALU instructions and, before those, the longest tile.  A wave alone on its
+// SIMD issues one instruction in about five cycles, so a tile's four waves take a fixed time per listed
+// face whatever else runs: 106 ns forward, 231 backward (whole tiles).  Hence
+//   * two faces per round: the forward one after the other, each record loaded from LDS a face ahead, the
+//     backward one in each half of the wave, two pixels a lane, so that one set of gradient sums
+//     serves both;
+//   * records staged by loads that go straight to LDS and need no registers;
+//   * long tiles of a single view split between two workgroups (Item);
+//   * little besides the walks where lists are short (an 8-view window: 42 faces a tile, 12 visits a
+//     wave): the backward takes the hit masks that the forward formed for the span still in LDS, the
+//     seeds' scales come from the host, wave maxima go by DPP.
+// One face per visit in whole tiles took 168 and 411 ns; the launches of the benchmark's 1200x680 view of
+// 1M faces 64 (forward), 124 (backward) and 183 us (fused), now 42, 88 and 121.
 #include "tsr_internal.h"
 
 namespace tsr {
@@ -64,8 +57,8 @@ struct Item {
 // columns, eight rows) of its quadrant, one pixel a lane of each half of the wave, so that both walks
 // take two faces per round at half the pixels' work.  A round's latency is what the longest tile costs,
 // and a split tile's is 0.6 to 0.7 of a whole one's; its work is 1.2 times as much.  So a tile is split
-// only where its own walk would outlast the launch: a listed face costs the tile 0.34 us, and the whole
-// card about 0.22 ns, so from K / kSplitDiv listed faces on (K: pairs of the binning), and from
+// only where its own walk would outlast the launch: a listed face costs the tile 0.34 us, and the
+// whole card about 0.22 ns, so from K / kSplitDiv listed faces on (K: pairs of the binning), and from
 // kSplitMin on, below which nothing is to be gained.  That does not happen to several views, whose
 // kernels are built without the split walks (their registers cost the 8-view window 2 %), and the few
 // workgroups of a small image gain nothing and wait for the larger kernel's instructions (64x48: the
@@ -74,8 +67,9 @@ struct Item {
 // twice as many FP32 additions; the backwards that may split therefore take the planes' moments about
 // the middle of the face (backward_walk).  A perspective-correct record has no room for it: those
 // backwards walk whole tiles.
-// One 1200x680 view of 1M faces: forward 73 -> 55 us, backward 128 -> 117, fused 161 -> 139, face
-// statistics 61 -> 48.
+// One 1200x680 view of 1M faces, whole tiles -> split, with a longest list of 594 faces: forward 74 -> 55 us,
+// backward 125 -> 118, fused 170 -> 135, face statistics 54 -> 48; of 539: forward 49 -> 42, backward
+// 90 -> 88, fused 141 -> 121.  Maps whose longest list is below some 300 faces gain nothing.
 constexpr uint32_t kSplitDiv = 1536, kSplitMin = 128;
 
 // Whether a backward in this mode may split tiles.
@@ -88,9 +82,8 @@ __device__ __forceinline__ int order_tile(const int* __restrict__ order, int i, 
   return t >= 0 && t < n_tiles ? t : -1;
 }
 
-// Item i of a launch (ONE: of a single view): without an order the XCD-interleaved tile ids (i: the workgroup); with the
-// longest-first order first the second halves of its first split_items tiles (none where the tile is
-// not split), then every tile, whole or its first half.
+// Item i of a launch in the longest-first order (ONE: of a single view): first the second halves of its
+// first split_items tiles (none where the tile is not split), then every tile, whole or its first half.
 template <bool ONE>
 __device__ __forceinline__ Item item_at(int i, const ViewTable& vt, const int* __restrict__ order,
                                         const uint32_t* __restrict__ ranges) {
@@ -1632,8 +1625,7 @@ __global__ __launch_bounds__(256) void k_vertex_gather(tsr_scene_dev sc, ViewTab
 
 // Set-up of a backward pass: zero the gradient accumulators of the visible (view, face) pairs
 // (one 16-byte store per thread, grid-stride); workgroup 0 also zeroes the per-view FP64 pose
-// and loss accumulators and the persistent kernel's queue counter, and builds the
-// longest-first tile order when `order` is given (tile counts the binning leaves it to).
+// and loss accumulators and the persistent kernel's queue counter.
 __global__ __launch_bounds__(256) void k_prep_bwd(ViewTable vt, const uint32_t* __restrict__ vis_total,
                                                   const uint32_t* __restrict__ vis_dense, acc_t* __restrict__ grad_acc,
                                                   float* __restrict__ sig_acc, float* __restrict__ persp_acc,

@@ -114,8 +114,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 // level is a transposing butterfly: a pair of vectors (a, b) becomes one, the lanes on one side of
 // the level's partner bit keeping a summed with their partner and the others keeping b.
 //
-// On gfx950 a wave64 v_permlane*_swap takes 8 cycles of a SIMD, a DPP add 4, a plain add or
-// multiply 2 (4 when nothing of the other kind can issue beside it).  The x levels are pairs of DPP
+// On gfx950 a wave64 v_permlane*_swap or reciprocal takes 8 cycles of a SIMD; a DPP add, a compare, a
+// select, a minimum or an integer instruction 4; an add, multiply or FMA 4 alone and 2.4 where those of
+// two waves issue together (a microbenchmark of each kind, many waves).  The x levels are pairs of DPP
 // row rotations that write only the banks of their side (a bank is four lanes; no select needed),
 // lane bits 1 and 0 quad permutes and a select, and only the last level, on the two vectors that are
 // left, a swap.  A lane that holds two pixels halves the sums' share of the work.

@@ -731,8 +731,8 @@ __device__ __forceinline__ void add_total(const GradLane& gl, uint32_t g, float 
 // record-parameter gradients are reduced over the wave and added to grad_acc.
 //   MID: the planes' moments are about the middle of the face's rectangle instead of its anchor
 // (GradField): five more instructions a round, which do not show in the times (1200x680 step of 1M
-// faces 243 us either way), and the colour gradients' error against 64 bits 1.0e-6 to 1.4e-6 -> 0.4e-6
-// to 0.5e-6 on a map with 161 split tiles, 5e-7 -> 2.8e-7 on one with 131.
+// faces 243 us either way), and the colour gradients' error against 64 bits 0.9e-6 to 1.4e-6 -> 0.4e-6
+// to 0.5e-6 on a map with 161 split tiles, 5.2e-7 -> 2.8e-7 on one with 131.
 template <int SM, bool COOP, bool SPLIT, bool MID, int SPAN = kSpan>
 __device__ __forceinline__ void backward_walk(const TileCtx& c, const float* __restrict__ records,
                                               const uint64_t* __restrict__ pairs, float sigma, int last, float Tb,
